@@ -35,17 +35,19 @@ struct DeviceLayout {
     uint64_t staging_stride = 0;
 };
 
-// K2 from HBM moves the device image in tiles of kTileBytes (kK2Lanes lanes x
-// kK2Vecs 16-byte vectors), one per workgroup.  Its plan holds, for each
-// block of kPlanBytes, the shift o_m - d_m from a destination byte to its
+// K2 from HBM moves the device image in tiles of kTileBytes (one 16-byte
+// vector for each of kK2Lanes lanes), one per workgroup.  Its plan holds, for
+// each block of kPlanBytes, the shift o_m - d_m from a destination byte to its
 // partition byte when the block lies inside the data bytes of one tensor m,
-// or kMixedTile when it meets a boundary or padding.
+// or kMixedTile + m when it meets a boundary or padding and its first byte
+// lies in the slot of tensor m (entries below kMixedEnd: a shift is at most
+// the size of an image).
 constexpr uint32_t kK2Lanes = 512;
-constexpr uint32_t kK2Vecs = 1;
-constexpr uint64_t kTileBytes = (uint64_t)kK2Lanes * 16 * kK2Vecs;
+constexpr uint64_t kTileBytes = (uint64_t)kK2Lanes * 16;
 constexpr uint64_t kPlanBytes = 16384;
-static_assert(kPlanBytes % kTileBytes == 0, "a tile lies in one plan block");
+static_assert(kPlanBytes == 2 * kTileBytes, "a workgroup moves both tiles of a mixed block");
 constexpr int64_t kMixedTile = INT64_MIN;
+constexpr int64_t kMixedEnd = INT64_MIN / 2;
 
 // Upload the tables, compute d on the device and check it against the host
 // plan `dev_off`/`dev_total`; allocate `staging_chunks` HBM chunks of `chunk`

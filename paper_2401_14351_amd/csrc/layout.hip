@@ -109,7 +109,22 @@ struct ScatterArgs {
     const uint8_t* run_src[kScatterBatch];
     uint64_t total;        // T
     uint32_t vec_ok;       // 16-byte aligned source vectors are addressable as such
-    uint64_t plan0;        // K2: plan entry of destination block p is shift[p - plan0]
+};
+
+// K2's arguments (an HBM source is one contiguous window, named as above).
+struct K2Args {
+    uint8_t* dst;
+    const uint64_t* off;
+    const uint64_t* size;
+    const uint64_t* dev;
+    uint64_t n;
+    uint64_t y0, y1;
+    uint64_t tile0;        // first tile of the launch
+    const uint8_t* base;
+    uint64_t x0, x1;
+    const int64_t* shift;  // the plan: entry of destination block p at shift[p - plan0]
+    uint64_t plan0;
+    uint32_t vec_ok;
 };
 
 // Where a launch's source bytes are: one contiguous window, a device table
@@ -117,9 +132,9 @@ struct ScatterArgs {
 // kind, so none of them pays for the others' addressing.
 enum SrcKind : int { kWindow = 0, kTable = 1, kRun = 2 };
 
-template <SrcKind K>
+template <SrcKind K, class Args = ScatterArgs>
 struct Src {
-    const ScatterArgs& a;
+    const Args& a;
     __device__ __forceinline__ const uint8_t* at(uint64_t x) const {
         if constexpr (K == kRun) {
             const uint64_t k = x / a.chunk;
@@ -157,6 +172,17 @@ __device__ __forceinline__ u32x4 funnel(u32x4 lo, u32x4 hi, uint32_t s) {
                            __builtin_amdgcn_alignbyte(w[6], w[5], b), __builtin_amdgcn_alignbyte(w[7], w[6], b)}; break;
     }
     return r;
+}
+
+// the same for an s that differs between lanes: selects instead of branches
+__device__ __forceinline__ u32x4 funnel_lanes(u32x4 lo, u32x4 hi, uint32_t s) {
+    const uint32_t b = s & 3;
+    const bool one = s & 4, two = s & 8;  // dwords to skip: one, then two more
+    const uint32_t m0 = one ? lo.y : lo.x, m1 = one ? lo.z : lo.y, m2 = one ? lo.w : lo.z, m3 = one ? hi.x : lo.w,
+                   m4 = one ? hi.y : hi.x, m5 = one ? hi.z : hi.y, m6 = one ? hi.w : hi.z;
+    const uint32_t q0 = two ? m2 : m0, q1 = two ? m3 : m1, q2 = two ? m4 : m2, q3 = two ? m5 : m3, q4 = two ? m6 : m4;
+    return u32x4{__builtin_amdgcn_alignbyte(q1, q0, b), __builtin_amdgcn_alignbyte(q2, q1, b),
+                 __builtin_amdgcn_alignbyte(q3, q2, b), __builtin_amdgcn_alignbyte(q4, q3, b)};
 }
 
 // keep bytes [0, keep) of v, zero the rest
@@ -207,6 +233,31 @@ __device__ __forceinline__ void st16(uint8_t* p, u32x4 v) {
     } else {
         *reinterpret_cast<u32x4*>(p) = v;
     }
+}
+
+// The destination vector at y read byte by byte: its dn data bytes from
+// partition byte x on where they lie in [lo, hi), zeros elsewhere.
+template <class S>
+__device__ __forceinline__ u32x4 bytes_vector(const S& src, uint64_t y, uint64_t lo, uint64_t hi, uint64_t x, uint32_t dn) {
+    uint64_t w0 = 0, w1 = 0;
+    for (uint32_t b = 0; b < dn; ++b) {
+        if (y + b < lo || y + b >= hi) continue;
+        const uint64_t v = (uint64_t)*src.at(x + b) << (8 * (b & 7));
+        if (b < 8) w0 |= v;
+        else w1 |= v;
+    }
+    return u32x4{(uint32_t)w0, (uint32_t)(w0 >> 32), (uint32_t)w1, (uint32_t)(w1 >> 32)};
+}
+
+// Store the vector at y: whole, or its bytes inside [lo, hi).
+template <bool NT>
+__device__ __forceinline__ void put_vector(uint8_t* dst, uint64_t y, uint64_t lo, uint64_t hi, bool whole, u32x4 v) {
+    if (whole) {
+        st16<NT>(dst + y, v);
+        return;
+    }
+    for (uint32_t b = 0; b < 16; ++b)
+        if (y + b >= lo && y + b < hi) dst[y + b] = (uint8_t)byte_of(v, b);
 }
 
 // Index entries of the tensors meeting a tile, staged in LDS.
@@ -284,11 +335,11 @@ __device__ __forceinline__ void scatter_span(const ScatterArgs& a, Staging& stg,
                 const uint64_t m = owner_global(a.dev, i_lo, i_lo + cnt - 1, y);
                 dm = a.dev[m]; om = a.off[m]; sm = a.size[m];
             }
+            const bool whole = y >= lo && y + 16 <= hi;  // vector entirely ours to write
+            if (whole) whole_mask |= 1u << u;
             const uint64_t r = y - dm;                   // byte of the slot
             const uint32_t dn = sm > r ? (sm - r < 16 ? (uint32_t)(sm - r) : 16u) : 0u;  // data bytes in vector
             const uint64_t x = om + r;                   // source of the vector's first byte
-            const bool whole = y >= lo && y + 16 <= hi;  // vector entirely ours to write
-            if (whole) whole_mask |= 1u << u;
             if (!dn) continue;
             const uint64_t xa = x & ~15ull;
             const uint32_t sh = (uint32_t)(x & 15);
@@ -298,24 +349,14 @@ __device__ __forceinline__ void scatter_span(const ScatterArgs& a, Staging& stg,
                 u32x4 w = sh == 0 ? v0 : funnel(v0, need == 32 ? ld16(src.at(xa + 16)) : v0, sh);
                 v[u] = dn < 16 ? keep_bytes(w, dn) : w;
             } else {
-                uint32_t w[4] = {0, 0, 0, 0};
-                for (uint32_t b = 0; b < dn; ++b) {
-                    if (y + b < lo || y + b >= hi) continue;
-                    w[b >> 2] |= (uint32_t)*src.at(x + b) << (8 * (b & 3));
-                }
-                v[u] = u32x4{w[0], w[1], w[2], w[3]};
+                v[u] = bytes_vector(src, y, lo, hi, x, dn);
             }
         }
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             if (!(in_mask >> u & 1)) continue;
             const uint64_t y = yt + ((uint64_t)u * L + threadIdx.x) * 16;
-            if (whole_mask >> u & 1) {
-                st16<NT>(a.dst + y, v[u]);
-            } else {
-                for (uint32_t b = 0; b < 16; ++b)
-                    if (y + b >= lo && y + b < hi) a.dst[y + b] = (uint8_t)byte_of(v[u], b);
-            }
+            put_vector<NT>(a.dst, y, lo, hi, whole_mask >> u & 1, v[u]);
         }
     }
 }
@@ -332,44 +373,125 @@ __global__ __launch_bounds__(kThreads) void k_scatter(ScatterArgs a) {
     scatter_span<kThreads, U, NT, K>(a, stg, t_begin, t_end);
 }
 
-// K2 from HBM: one kTileBytes destination tile per workgroup of kK2Lanes
-// lanes, tiles in dispatch order, so the workgroups in flight sweep a
-// contiguous window of both images (HBM serves that order best).  A tile
-// whose plan block lies inside one tensor's data, and whose source bytes all
-// lie in the window, copies straight from source byte y + shift: one table
-// load, then the data loads.  Every other tile (tensor boundaries, padding,
-// window edges) takes the general path of scatter_span.
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, uint32_t lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// The vector at destination byte y from partition byte xs + at, where xs is
+// the same for the whole wave, and so the shift.
 template <bool NT>
-__global__ __launch_bounds__(kK2Lanes) void k2_tiles(ScatterArgs a, const int64_t* __restrict__ shift) {
-    constexpr uint32_t U = kK2Vecs;
-    __shared__ Staging stg;
+__device__ __forceinline__ void copy16(const K2Args& a, uint64_t y, uint64_t xs, uint32_t at) {
+    const uint32_t r = (uint32_t)(xs & 15);
+    // partition byte x sits at base + (x - x0); base and x0 are 16-byte aligned
+    const uint8_t* p = a.base + (xs - a.x0) + at - r;
+    st16<NT>(a.dst + y, r == 0 ? ld16(p) : funnel(ld16(p), ld16(p + 16), r));
+}
+
+// The calling wave's kilobyte of a tile of K2 that does not lie inside one
+// tensor's data: a boundary, padding, a window edge.  `w` is a tensor whose
+// slot starts at or before the tile.  The wave loads the index entries of 64
+// tensors from w on in one go, one per lane, and finds by ballot which of
+// them own its bytes; those, mostly one or two, go round the wave by scalar
+// lane reads and every lane keeps the last that starts at or before its
+// vector.  Only a wave that meets (or follows, within its plan block) more
+// than 64 tensors loads another 64.
+template <bool NT>
+__device__ __forceinline__ void k2_mixed(const K2Args& a, uint64_t yt, uint64_t w) {
+    const Src<kWindow, K2Args> src{a};
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t yw = yt + 1024 * (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t lo = yw > a.y0 ? yw : a.y0;
+    const uint64_t hi = yw + 1024 < a.y1 ? yw + 1024 : a.y1;
+    if (lo >= hi) return;
+    const uint64_t y = yw + lane * 16;
+    uint64_t dm = 0, om = 0, sm = 0;
+    for (;;) {
+        const uint64_t i = w + lane;
+        const bool in = i < a.n;
+        const uint64_t d = in ? a.dev[i] : ~0ull, o = in ? a.off[i] : 0, s = in ? a.size[i] : 0;
+        const uint64_t next = w + 64 < a.n ? a.dev[w + 64] : ~0ull;  // start of the first slot past these
+        const uint32_t before = __popcll(__ballot(d <= lo)), last = __popcll(__ballot(d < hi));
+        const uint32_t first = before ? before - 1 : 0;
+        if (last == first + 1 && next >= hi && hi - lo == 1024) {
+            const uint64_t dk = readlane64(d, first);
+            if (dk <= lo && hi <= dk + readlane64(s, first)) {
+                const uint64_t xs = readlane64(o, first) + (lo - dk);
+                if (src.vectors_ok(xs & ~15ull, 1040)) {
+                    copy16<NT>(a, y, xs, lane * 16);
+                    return;
+                }
+            }
+        }
+        for (uint32_t k = first; k < last; ++k) {
+            const uint64_t dk = readlane64(d, k), ok = readlane64(o, k), sk = readlane64(s, k);
+            if (y >= dk) {
+                dm = dk;
+                om = ok;
+                sm = sk;
+            }
+        }
+        if (next >= hi) break;
+        w += 64;
+    }
+    if (y + 16 <= lo || y >= hi) return;
+    const uint64_t r = y - dm;                                                   // byte of the slot
+    const uint32_t dn = sm > r ? (sm - r < 16 ? (uint32_t)(sm - r) : 16u) : 0u;  // data bytes in the vector
+    const uint64_t x = om + r;                                                   // source of its first byte
+    const bool whole = y >= lo && y + 16 <= hi;                                  // entirely ours to write
+    u32x4 v = {0, 0, 0, 0};
+    if (dn) {
+        const uint64_t xa = x & ~15ull;
+        const uint32_t sh = (uint32_t)(x & 15);
+        const bool two = sh + dn > 16;  // the data span two aligned source vectors
+        if (whole && src.vectors_ok(xa, two ? 32 : 16)) {
+            const u32x4 v0 = ld16(src.at(xa));
+            v = keep_bytes(funnel_lanes(v0, two ? ld16(src.at(xa + 16)) : v0, sh), dn);
+        } else {
+            v = bytes_vector(src, y, lo, hi, x, dn);
+        }
+    }
+    put_vector<NT>(a.dst, y, lo, hi, whole, v);
+}
+
+// K2 from HBM: one kTileBytes destination tile per workgroup of kK2Lanes
+// lanes, one vector per lane, tiles in dispatch order, so the workgroups in
+// flight sweep a contiguous window of both images (HBM serves that order
+// best).  A tile whose plan block lies inside one tensor's data, and whose
+// source bytes all lie in the window, copies straight from source byte
+// y + shift: one table load, then the data loads.  The waves of every other
+// tile take k2_mixed, from the tensor the plan entry names.
+//
+// Four workgroups fit a CU, and the copy needs all four.  With more than 80
+// SGPRs a wave (the hardware takes them in steps of 16 and keeps 16 back) only
+// seven waves fit a SIMD, so three workgroups a CU: a 2.1 GB repack of straight
+// tiles took 680 us with 91 SGPRs and 646 us (6.5 TB/s) with 62 to 78.
+template <bool NT>
+__global__ __launch_bounds__(kK2Lanes) __attribute__((amdgpu_num_sgpr(80))) void k2_tiles(K2Args a) {
     const uint64_t t = a.tile0 + blockIdx.x;
     const uint64_t yt = t * kTileBytes;
-    const int64_t sh = shift[yt / kPlanBytes - a.plan0];
-    if (sh != kMixedTile && yt >= a.y0 && yt + kTileBytes <= a.y1) {
+    const int64_t sh = a.shift[yt / kPlanBytes - a.plan0];
+    if (sh < kMixedEnd) {
+        k2_mixed<NT>(a, yt, (uint64_t)(sh - kMixedTile));
+        return;
+    }
+    if (yt >= a.y0 && yt + kTileBytes <= a.y1) {
         const uint64_t xs = yt + (uint64_t)sh;  // source of the tile's first byte
         // aligned 16-byte source vectors spanning [xs, xs + S)
         const uint64_t xa0 = xs & ~15ull, xa1 = (xs + kTileBytes + 15) & ~15ull;
         if (a.vec_ok && xa0 >= a.x0 && xa1 <= a.x1) {
-            const uint32_t r = (uint32_t)(xs & 15);  // the same for every vector of the tile
-            u32x4 v[U];
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                // partition byte x sits at base + (x - x0); base and x0 are 16-byte aligned
-                const uint8_t* p = a.base + (xs - a.x0) + ((uint64_t)u * kK2Lanes + threadIdx.x) * 16 - r;
-                v[u] = r == 0 ? ld16(p) : funnel(ld16(p), ld16(p + 16), r);
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) st16<NT>(a.dst + yt + ((uint64_t)u * kK2Lanes + threadIdx.x) * 16, v[u]);
+            copy16<NT>(a, yt + threadIdx.x * 16, xs, threadIdx.x * 16);
             return;
         }
     }
-    scatter_span<kK2Lanes, U, NT, kWindow>(a, stg, blockIdx.x, blockIdx.x + 1);
+    // a straight block cut by the window's edge names no tensor: search for it
+    k2_mixed<NT>(a, yt, owner_global(a.dev, 0, a.n - 1, yt));
 }
 
 // K2's plan for destination blocks p0 .. p0 + n_blocks - 1: shift[p - p0] =
 // o_m - d_m when block p (kPlanBytes) lies inside the data bytes of tensor
-// m, else kMixedTile.
+// m, else kMixedTile + m, m being the tensor whose slot holds its first byte.
 __global__ __launch_bounds__(256) void k3_tile_shift(const uint64_t* __restrict__ dev, const uint64_t* __restrict__ off,
                                                      const uint64_t* __restrict__ size, uint64_t n, uint64_t p0,
                                                      uint64_t n_blocks, int64_t* __restrict__ shift) {
@@ -377,7 +499,7 @@ __global__ __launch_bounds__(256) void k3_tile_shift(const uint64_t* __restrict_
     for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n_blocks; p += stride) {
         const uint64_t y = (p0 + p) * kPlanBytes;
         const uint64_t m = owner_global(dev, 0, n - 1, y);  // d_0 = 0 <= y
-        shift[p] = y + kPlanBytes <= dev[m] + size[m] ? (int64_t)(off[m] - dev[m]) : kMixedTile;
+        shift[p] = y + kPlanBytes <= dev[m] + size[m] ? (int64_t)(off[m] - dev[m]) : kMixedTile + (int64_t)m;
     }
 }
 
@@ -404,7 +526,7 @@ uint64_t y_of(const DeviceLayout& l, uint64_t x) {
 // for HBM sources; SLLM_K2_UNROLL (4 or 8 vectors per lane) and
 // SLLM_K1_BLOCKS / SLLM_K1_STREAM_BLOCKS (grid of a launch that moves the
 // whole image / part of it, as for K1) for host sources.
-int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream_t stream) {
+int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream_t stream, uint64_t plan0 = 0) {
     a.off = l.d_off;
     a.size = l.d_size;
     a.dev = l.d_dev;
@@ -415,17 +537,30 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
     if (!src_is_host) {  // HBM source (K2): one tile per workgroup
         if (!l.d_shift) return fail(SLLM_E_INVAL, "scatter: the layout has no tile plan");
         const bool nt = env_uint("SLLM_K2_NT", 1) != 0;
+        K2Args k{};
+        k.dst = a.dst;
+        k.off = a.off;
+        k.size = a.size;
+        k.dev = a.dev;
+        k.n = a.n;
+        k.y0 = a.y0;
+        k.y1 = a.y1;
+        k.base = a.base;
+        k.x0 = a.x0;
+        k.x1 = a.x1;
+        k.shift = l.d_shift;
+        k.plan0 = plan0;
+        k.vec_ok = a.vec_ok;
         const uint64_t t_end = ceil_div(a.y1, kTileBytes);
         // at most 2^31 lanes a launch (SLLM_K2_MAX_GRID lowers it, to exercise
         // the split on small images)
         constexpr uint64_t kMaxGrid = (1ull << 31) / kK2Lanes;
         const uint64_t max_grid = std::max<uint64_t>(1, std::min<uint64_t>(kMaxGrid, env_uint("SLLM_K2_MAX_GRID", kMaxGrid)));
         for (uint64_t t0 = a.y0 / kTileBytes; t0 < t_end; t0 += max_grid) {
-            a.tile0 = t0;
-            a.n_tiles = std::min(max_grid, t_end - t0);
-            const dim3 grid((uint32_t)a.n_tiles);
-            if (nt) k2_tiles<true><<<grid, dim3(kK2Lanes), 0, stream>>>(a, l.d_shift);
-            else k2_tiles<false><<<grid, dim3(kK2Lanes), 0, stream>>>(a, l.d_shift);
+            k.tile0 = t0;
+            const dim3 grid((uint32_t)std::min(max_grid, t_end - t0));
+            if (nt) k2_tiles<true><<<grid, dim3(kK2Lanes), 0, stream>>>(k);
+            else k2_tiles<false><<<grid, dim3(kK2Lanes), 0, stream>>>(k);
             SLLM_HIP(hipGetLastError());
         }
         return SLLM_OK;
@@ -658,8 +793,7 @@ int32_t repack_noalloc(const IndexData& ix, int device, uint64_t dev_align, uint
         a.vec_ok = reinterpret_cast<uintptr_t>(src) % 16 == 0;
         a.y0 = p0 * kPlanBytes;
         a.y1 = std::min((p0 + nb) * kPlanBytes, dev_total);
-        a.plan0 = p0;
-        SLLM_TRY(launch(l, a, /*src_is_host=*/false, stream));
+        SLLM_TRY(launch(l, a, /*src_is_host=*/false, stream, p0));
     }
     return SLLM_OK;
 }

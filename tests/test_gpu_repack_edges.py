@@ -1,0 +1,57 @@
+"""The HBM repack at the edges of its tiles: slots that end a byte before,
+at and after a wave's kilobyte, a tile (8 KiB) and a plan block (16 KiB), runs
+of zero-size tensors longer than the 64 entries a wave loads at a time, and
+launches split so that they start and end inside plan blocks.  Byte for byte
+against the oracle."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2401_14351_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+SENTINEL = 0xA5
+
+
+def edge_sizes():
+    sizes = []
+    for base in (1 << 10, 8 << 10, 16 << 10):
+        for k in (1, 2, 3):
+            sizes += [k * base + d for d in (-17, -16, -1, 0, 1, 15, 16)]
+    sizes += [0] * 70 + [5000] + [0] * 130  # more empty slots in one place than a wave loads
+    sizes += [1 + i % 16 for i in range(300)] + [40_000] + [16] * 65 + [0] + [2000]
+    return sizes
+
+
+def checkpoint(d, A):
+    rng = np.random.default_rng(A)
+    tensors = [(f"t{i}", "i8", (n,), rng.integers(0, 256, n, dtype=np.uint8)) for i, n in enumerate(edge_sizes())]
+    binding.convert(iter(tensors), d, A, 1 << 16)
+    index = oracle.make_index(tensors, A, 1)
+    return index, bytes(oracle.partition_bytes(tensors, A)[:index.total_bytes])
+
+
+@pytest.mark.parametrize("A", [1, 16, 256])
+@pytest.mark.parametrize("grid", [0, 1, 3])
+def test_repack_edges(tmp_path, monkeypatch, A, grid):
+    import torch
+
+    index, image = checkpoint(str(tmp_path), A)
+    src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+    if grid:
+        monkeypatch.setenv("SLLM_K2_MAX_GRID", str(grid))
+        monkeypatch.setenv("SLLM_NOALLOC_PLAN_BLOCKS", "5")
+    for A2 in (16, 64, 4096):
+        print("[gpu-test] repack edges", A, grid, A2, flush=True)
+        want = bytes(oracle.repack(image, index, A2))
+        for noalloc in (False, True):
+            dst = torch.full((len(want) + 64,), SENTINEL, dtype=torch.uint8, device="cuda:0")
+            with binding.Checkpoint(str(tmp_path), dev_alignment=A2) as ck:
+                (ck.repack_noalloc if noalloc else ck.repack)(src, dst)
+                torch.cuda.synchronize()
+            got = dst.cpu().numpy()
+            bad = np.nonzero(got[:len(want)] != np.frombuffer(want, np.uint8))[0]
+            assert bad.size == 0, (A2, noalloc, bad[:8].tolist())
+            assert (got[len(want):] == SENTINEL).all(), "bytes past the image were written"
