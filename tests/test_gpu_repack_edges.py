@@ -1,8 +1,9 @@
 """The HBM repack at the edges of its tiles: slots that end a byte before,
 at and after a wave's kilobyte, a tile (8 KiB) and a plan block (16 KiB), runs
 of zero-size tensors longer than the 64 entries a wave loads at a time, and
-launches split so that they start and end inside plan blocks.  Byte for byte
-against the oracle."""
+launches split so that they start and end inside plan blocks; and the size
+tables of the allocation-free repack at every width they are packed in.  Byte
+for byte against the oracle."""
 
 import numpy as np
 import pytest
@@ -55,3 +56,40 @@ def test_repack_edges(tmp_path, monkeypatch, A, grid):
             bad = np.nonzero(got[:len(want)] != np.frombuffer(want, np.uint8))[0]
             assert bad.size == 0, (A2, noalloc, bad[:8].tolist())
             assert (got[len(want):] == SENTINEL).all(), "bytes past the image were written"
+
+
+# sizes of n tensors: all equal (no bits), multiples of a power of two, one
+# large among small (wide values), and batch ends at 1,988 and 2,048 tensors
+TABLES = {
+    "equal": [513] * 2049,
+    "shifted": [4096 * (1 + i % 5) for i in range(700)],
+    "wide": [(i * 7919) % 301 for i in range(2500)] + [(9 << 20) + 5] + [i % 3 for i in range(40)],
+    "16 bits": [1 + (i * 40503) % 4999 + (65000 if i % 900 == 0 else 0) for i in range(1990)],
+    "one": [77],
+    "zeros": [0] * 2047 + [3, 0, 0],
+}
+
+
+@pytest.mark.parametrize("name", sorted(TABLES))
+def test_noalloc_tables(tmp_path, monkeypatch, name):
+    import torch
+
+    rng = np.random.default_rng(7)
+    tensors = [(f"t{i}", "i8", (n,), rng.integers(0, 256, n, dtype=np.uint8)) for i, n in enumerate(TABLES[name])]
+    binding.convert(iter(tensors), str(tmp_path), 64, 1 << 16)
+    index = oracle.make_index(tensors, 64, 1)
+    image = bytes(oracle.partition_bytes(tensors, 64)[:index.total_bytes])
+    src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+    for A2, blocks in ((16, None), (256, "7"), (4096, None)):
+        print("[gpu-test] noalloc tables", name, A2, flush=True)
+        if blocks:
+            monkeypatch.setenv("SLLM_NOALLOC_PLAN_BLOCKS", blocks)
+        want = np.frombuffer(bytes(oracle.repack(image, index, A2)), np.uint8)
+        dst = torch.full((len(want) + 64,), SENTINEL, dtype=torch.uint8, device="cuda:0")
+        with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+            ck.repack_noalloc(src, dst, A2)
+            torch.cuda.synchronize()
+        got = dst.cpu().numpy()
+        assert np.array_equal(got[:len(want)], want)
+        assert (got[len(want):] == SENTINEL).all(), "bytes past the image were written"
+        monkeypatch.delenv("SLLM_NOALLOC_PLAN_BLOCKS", raising=False)
