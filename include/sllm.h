@@ -39,6 +39,10 @@
  *     on the same device (at most 32 sets per process, kept until the
  *     process ends), so opening a handle per load costs no stream creation.
  *     A caller that resets a device must not use the library afterwards.
+ *   - The device tables and HBM staging of a handle with a dev_alignment go
+ *     back to the library at close and stay idle for the next handle (at most
+ *     64 MiB in 32 blocks per device; more is freed, and the idle ones are
+ *     freed when an allocation of theirs finds no memory).
  *   - Reader threads outlive the loads that start them: a finished reader
  *     waits idle (at most 64 per process, until the process ends) for the
  *     next load or pool fill, which then wakes it instead of starting a

@@ -3,7 +3,7 @@
 // closed form of Sec. 4.1's aligned packing, applied with A2).
 //
 // The device keeps the index as three u64 tables (file offsets o, sizes s and
-// device offsets d, the last computed on the GPU by a wave64 prefix sum) and
+// device offsets d, both offsets computed on the GPU by wave64 prefix sums) and
 // a scatter kernel moves a window [x0, x1) of partition bytes to the device
 // bytes that window owns: the data bytes whose source lies in the window plus
 // the padding after every tensor whose last byte lies in it.  Windows that
@@ -14,11 +14,26 @@
 
 #include <climits>
 #include <cstdint>
-#include <vector>
 
 #include "format.hpp"
 
 namespace sllm {
+
+// Device memory that outlives the handle that took it: a block given back stays
+// idle, up to kMaxIdleBlockBytes and kMaxIdleBlocks a device, for the next
+// handle, so opening and closing a handle per load costs no allocation and no
+// hipFree (which waits for the whole device).  A block may be given back once
+// no work uses it.  An allocation that fails frees the idle blocks and tries
+// again.  Safe from several threads.
+struct DeviceBlock {
+    int device = 0;
+    uint8_t* p = nullptr;
+    uint64_t bytes = 0;  // capacity
+};
+constexpr uint64_t kMaxIdleBlockBytes = 64ull << 20;
+constexpr size_t kMaxIdleBlocks = 32;
+int32_t block_take(int device, uint64_t bytes, DeviceBlock* out);  // `device` is current
+void block_give(DeviceBlock* b);                                   // b's device is current
 
 struct DeviceLayout {
     uint64_t n = 0;                 // tensors
@@ -28,11 +43,13 @@ struct DeviceLayout {
     uint64_t* d_off = nullptr;      // device: o_i
     uint64_t* d_size = nullptr;     // device: s_i
     uint64_t* d_dev = nullptr;      // device: d_i for i < n, d_n = T2
-    std::vector<uint64_t> h_off, h_dev, h_end;  // host: o_i, d_i, o_i + s_i
+    const TensorRec* tensors = nullptr;  // host: the index records, n of them
+    const uint64_t* h_dev = nullptr;     // host: d_i
     int64_t* d_shift = nullptr;     // device: K2's plan, one entry per kPlanBytes of the device image
     uint64_t n_shift = 0;           // entries of d_shift: ceil(T2 / kPlanBytes)
     uint8_t* staging = nullptr;     // HBM staging chunks for copy-engine loads
     uint64_t staging_stride = 0;
+    DeviceBlock tables, stage;      // device memory of the tables and plan, and of the staging chunks
 };
 
 // K2 from HBM moves the device image in tiles of kTileBytes (one 16-byte
@@ -49,12 +66,13 @@ static_assert(kPlanBytes == 2 * kTileBytes, "a workgroup moves both tiles of a m
 constexpr int64_t kMixedTile = INT64_MIN;
 constexpr int64_t kMixedEnd = INT64_MIN / 2;
 
-// Upload the tables, compute d on the device and check it against the host
-// plan `dev_off`/`dev_total`; allocate `staging_chunks` HBM chunks of `chunk`
-// bytes when asked.
-int32_t device_layout_build(const std::vector<uint64_t>& file_off, const std::vector<uint64_t>& sizes,
-                            const std::vector<uint64_t>& dev_off, uint64_t total, uint64_t dev_total,
+// Compute the tables and K2's plan on the device for the layout of `ix` at
+// dev_align (host offsets dev_off, dev_total bytes; both arguments must outlive
+// the layout), with `staging_chunks` HBM chunks of `chunk` bytes when asked.
+// The tables are complete on return.  The current device must be `device`.
+int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev_off, uint64_t dev_total,
                             uint64_t dev_align, uint64_t staging_chunks, uint64_t chunk, DeviceLayout* out);
+// No work may use the layout any more; its device must be current.
 void device_layout_free(DeviceLayout* l);
 
 // Move partition window [x0, x1), held contiguously at `src` (device memory,

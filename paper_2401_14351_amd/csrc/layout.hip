@@ -1,21 +1,20 @@
 // gfx950 kernels for device layouts with alignment A2.
 //
-// K3  offsets scan: d = exclusive prefix sum of align_up(s_i, A2) over the
-//     tensor index, one workgroup of 16 wave64s: a shuffle scan inside each
-//     wave, the 16 wave totals combined through LDS, a running carry across
-//     blocks of 1024 tensors.
+// K3  index tables: o and d are the exclusive prefix sums of align_up(s_i, A)
+//     and align_up(s_i, A2), scanned on the device from sizes that travel as
+//     kernel arguments, about 2,000 tensors a launch, together with K2's plan.
 // K2  index-driven scatter from HBM (the repack of a file-layout image, and
 //     copy-engine loads staged in HBM): destination-driven, one 8 KiB tile of
 //     the device image per workgroup of 512 lanes, tiles in dispatch order.
-//     A plan built with the layout gives, per 16 KiB block of the device
-//     image, the shift from a destination byte to its partition byte when the
-//     block lies inside one tensor's data; such tiles copy with one 16-byte
-//     vector per lane after a single table load.  The other tiles take the
-//     general path below.
-// K1-scatter (mapped pinned host source) and K2's general path: each
-//     workgroup walks a span of tiles, finds the tensors whose slots meet a
-//     tile (a forward search of d), stages those index entries in LDS and
-//     keeps them for the following tiles they still cover; every lane
+//     The plan gives, per 16 KiB block of the device image, the shift from a
+//     destination byte to its partition byte when the block lies inside one
+//     tensor's data; such tiles copy with one 16-byte vector per lane after a
+//     single table load.  The waves of the other tiles start from the tensor
+//     the plan names.
+// K1-scatter (mapped pinned host source): each workgroup walks a span of
+//     tiles, finds the tensors whose slots meet a tile (a forward search of
+//     d), stages those index entries in LDS and keeps them for the following
+//     tiles they still cover; every lane
 //     produces aligned 16-byte destination vectors: a straight 16-byte load
 //     when source and destination agree mod 16, two aligned loads and a byte
 //     funnel shift when they do not, zeros for padding.  Only vectors cut by
@@ -26,6 +25,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <vector>
 
 #include "common.hpp"
 #include "device_layout.hpp"
@@ -63,31 +63,6 @@ __device__ __forceinline__ uint64_t wave_scan(uint64_t x) {
     x += dpp64<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
     x += dpp64<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
     return x;
-}
-
-__global__ __launch_bounds__(1024) void k3_offsets_scan(const uint64_t* __restrict__ size, uint64_t n,
-                                                        uint64_t align, uint64_t* __restrict__ dev) {
-    __shared__ uint64_t wave_tot[16];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t carry = 0;
-    for (uint64_t base = 0; base < n; base += 1024) {
-        const uint64_t i = base + threadIdx.x;
-        const uint64_t v = i < n ? (size[i] + align - 1) & ~(align - 1) : 0;
-        const uint64_t incl = wave_scan(v);
-        if (lane == 63) wave_tot[wave] = incl;
-        __syncthreads();
-        if (wave == 0) {
-            uint64_t w = lane < 16 ? wave_tot[lane] : 0;
-            w = wave_scan(w);
-            if (lane < 16) wave_tot[lane] = w;
-        }
-        __syncthreads();
-        const uint64_t before = carry + (wave ? wave_tot[wave - 1] : 0);
-        if (i < n) dev[i] = before + incl - v;
-        carry += wave_tot[15];
-        __syncthreads();  // wave_tot is rewritten by the next block
-    }
-    if (threadIdx.x == 0) dev[n] = carry;
 }
 
 // The plan entry of the block at destination byte y, whose first byte lies in
@@ -633,10 +608,10 @@ uint32_t env_uint(const char* name, uint32_t dflt) {
 // first device byte owned by partition byte x: the first tensor whose data
 // ends after x starts owning there (padding belongs to a tensor's last byte)
 uint64_t y_of(const DeviceLayout& l, uint64_t x) {
-    auto it = std::upper_bound(l.h_end.begin(), l.h_end.end(), x);
-    if (it == l.h_end.end()) return l.dev_total;
-    const size_t i = (size_t)(it - l.h_end.begin());
-    return l.h_dev[i] + (x > l.h_off[i] ? x - l.h_off[i] : 0);
+    const TensorRec* end = l.tensors + l.n;
+    const TensorRec* t = std::upper_bound(l.tensors, end, x, [](uint64_t v, const TensorRec& r) { return v < r.offset + r.nbytes; });
+    if (t == end) return l.dev_total;
+    return l.h_dev[t - l.tensors] + (x > t->offset ? x - t->offset : 0);
 }
 
 // Launch shape, read at every launch so that one process can compare shapes:
@@ -701,121 +676,6 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
 }
 
 }  // namespace
-
-int32_t device_layout_build(const std::vector<uint64_t>& file_off, const std::vector<uint64_t>& sizes,
-                            const std::vector<uint64_t>& dev_off, uint64_t total, uint64_t dev_total,
-                            uint64_t dev_align, uint64_t staging_chunks, uint64_t chunk, DeviceLayout* out) {
-    DeviceLayout& l = *out;
-    l.n = sizes.size();
-    l.total = total;
-    l.dev_total = dev_total;
-    l.dev_align = dev_align;
-    l.h_off = file_off;
-    l.h_dev = dev_off;
-    l.h_end.resize(l.n);
-    for (uint64_t i = 0; i < l.n; ++i) l.h_end[i] = file_off[i] + sizes[i];
-    if (staging_chunks) {
-        if (!align_up(chunk, 256, &l.staging_stride)) return fail(SLLM_E_INVAL, "chunk size overflows");
-        SLLM_HIP(hipMalloc(reinterpret_cast<void**>(&l.staging), staging_chunks * l.staging_stride));
-    }
-    if (l.n == 0) return SLLM_OK;
-    const size_t bytes = l.n * sizeof(uint64_t);
-    SLLM_HIP(hipMalloc(reinterpret_cast<void**>(&l.d_off), bytes));
-    SLLM_HIP(hipMalloc(reinterpret_cast<void**>(&l.d_size), bytes));
-    SLLM_HIP(hipMalloc(reinterpret_cast<void**>(&l.d_dev), bytes + sizeof(uint64_t)));
-    SLLM_HIP(hipMemcpy(l.d_off, file_off.data(), bytes, hipMemcpyHostToDevice));
-    SLLM_HIP(hipMemcpy(l.d_size, sizes.data(), bytes, hipMemcpyHostToDevice));
-    k3_offsets_scan<<<dim3(1), dim3(1024), 0, nullptr>>>(l.d_size, l.n, dev_align, l.d_dev);
-    SLLM_HIP(hipGetLastError());
-    // K2's tile plan, from the scanned offsets (same stream, so in order)
-    l.n_shift = ceil_div(dev_total, kPlanBytes);
-    if (l.n_shift) {
-        SLLM_HIP(hipMalloc(reinterpret_cast<void**>(&l.d_shift), l.n_shift * sizeof(int64_t)));
-        const uint64_t blocks = std::min<uint64_t>(ceil_div(l.n_shift, 256), 4096);
-        k3_tile_shift<<<dim3((uint32_t)blocks), dim3(256), 0, nullptr>>>(l.d_dev, l.d_off, l.d_size, l.n, 0,
-                                                                         l.n_shift, l.d_shift);
-        SLLM_HIP(hipGetLastError());
-    }
-    std::vector<uint64_t> got(l.n + 1);
-    SLLM_HIP(hipMemcpy(got.data(), l.d_dev, bytes + sizeof(uint64_t), hipMemcpyDeviceToHost));
-    for (uint64_t i = 0; i < l.n; ++i)
-        if (got[i] != dev_off[i])
-            return fail(SLLM_E_HIP, "device offsets scan disagrees at tensor %llu: %llu vs %llu", (unsigned long long)i,
-                        (unsigned long long)got[i], (unsigned long long)dev_off[i]);
-    if (got[l.n] != dev_total) return fail(SLLM_E_HIP, "device offsets scan total disagrees");
-    return SLLM_OK;
-}
-
-void device_layout_free(DeviceLayout* l) {
-    for (void* p : {(void*)l->d_off, (void*)l->d_size, (void*)l->d_dev, (void*)l->d_shift, (void*)l->staging})
-        if (p) (void)hipFree(p);
-    *l = DeviceLayout{};
-}
-
-int32_t launch_scatter_window(const DeviceLayout& l, uint8_t* dst, const uint8_t* src, uint64_t x0, uint64_t x1,
-                              bool src_is_host, hipStream_t stream) {
-    ScatterArgs a{};
-    a.dst = dst;
-    a.base = src;
-    a.x0 = x0;
-    a.x1 = x1;
-    a.vec_ok = (reinterpret_cast<uintptr_t>(src) % 16 == 0) && (x0 % 16 == 0);
-    a.y0 = y_of(l, x0);
-    a.y1 = y_of(l, x1);
-    return launch(l, a, src_is_host, stream);
-}
-
-int32_t launch_scatter_run(const DeviceLayout& l, uint8_t* dst, const uint8_t* const* srcs, uint64_t k0, uint32_t m,
-                           uint64_t chunk, hipStream_t stream) {
-    if (m == 0) return SLLM_OK;
-    if (m > kScatterBatch || chunk == 0) return fail(SLLM_E_INVAL, "scatter run: bad size");
-    if (k0 >= ceil_div(l.total, chunk) || m > ceil_div(l.total, chunk) - k0)
-        return fail(SLLM_E_INVAL, "scatter run: chunks past the end of the image");
-    ScatterArgs a{};
-    a.dst = dst;
-    a.chunk = chunk;
-    a.run_n = m;
-    a.run_k0 = k0;
-    bool aligned = chunk % 16 == 0;
-    for (uint32_t j = 0; j < m; ++j) {
-        a.run_src[j] = srcs[j];
-        aligned = aligned && reinterpret_cast<uintptr_t>(srcs[j]) % 16 == 0;
-    }
-    a.vec_ok = aligned;
-    a.x0 = k0 * chunk;
-    a.x1 = std::min((k0 + m) * chunk, l.total);
-    a.y0 = y_of(l, a.x0);
-    a.y1 = y_of(l, a.x1);
-    return launch(l, a, /*src_is_host=*/true, stream);
-}
-
-int32_t launch_scatter_table(const DeviceLayout& l, uint8_t* dst, const uint8_t* const* table, uint64_t chunk,
-                             hipStream_t stream) {
-    ScatterArgs a{};
-    a.dst = dst;
-    a.table = table;
-    a.chunk = chunk;
-    a.vec_ok = chunk % 16 == 0;
-    a.y0 = 0;
-    a.y1 = l.dev_total;
-    return launch(l, a, /*src_is_host=*/true, stream);
-}
-
-}  // namespace sllm
-
-// ---------------------------------------------------------------------------
-// Allocation-free repack
-// ---------------------------------------------------------------------------
-
-// The device memory of the allocation-free repack: the size table, the two
-// scanned offset tables and one window of K2's plan (layout in
-// device_layout.hpp).  Every device holds its own copy from the library's
-// first kernel launch on it until the process ends.  Host code reaches a
-// device's copy only through the address hipGetSymbolAddress returns with
-// that device current; the name itself is not a device address on the host.
-static __device__ __align__(256) uint8_t scratch[sllm::kNoAllocScratchBytes];
-
-namespace sllm {
 
 namespace {
 
@@ -887,6 +747,184 @@ int32_t launch_tables(const std::vector<TensorRec>& t, uint64_t align, uint64_t 
     }
     return SLLM_OK;
 }
+
+std::mutex g_blocks_mu;
+std::vector<DeviceBlock> g_idle_blocks;
+
+}  // namespace
+
+int32_t block_take(int device, uint64_t bytes, DeviceBlock* out) {
+    constexpr uint64_t kGrain = 64 << 10;
+    *out = DeviceBlock{};
+    out->device = device;
+    if (bytes == 0) return SLLM_OK;
+    if (bytes > UINT64_MAX - kGrain) return fail(SLLM_E_INVAL, "block size overflows");
+    const uint64_t want = (bytes + kGrain - 1) / kGrain * kGrain;
+    {
+        // the smallest idle block that fits, unless it would waste most of itself
+        std::lock_guard<std::mutex> g(g_blocks_mu);
+        size_t best = g_idle_blocks.size();
+        for (size_t i = 0; i < g_idle_blocks.size(); ++i) {
+            const DeviceBlock& b = g_idle_blocks[i];
+            if (b.device != device || b.bytes < want || b.bytes / 4 > want) continue;
+            if (best == g_idle_blocks.size() || b.bytes < g_idle_blocks[best].bytes) best = i;
+        }
+        if (best < g_idle_blocks.size()) {
+            *out = g_idle_blocks[best];
+            g_idle_blocks.erase(g_idle_blocks.begin() + (long)best);
+            return SLLM_OK;
+        }
+    }
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, want);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();  // leave no error behind for later launch checks
+        std::vector<DeviceBlock> idle;
+        {
+            std::lock_guard<std::mutex> g(g_blocks_mu);
+            for (size_t i = 0; i < g_idle_blocks.size();) {
+                if (g_idle_blocks[i].device != device) {
+                    ++i;
+                    continue;
+                }
+                idle.push_back(g_idle_blocks[i]);
+                g_idle_blocks.erase(g_idle_blocks.begin() + (long)i);
+            }
+        }
+        for (const DeviceBlock& b : idle) (void)hipFree(b.p);
+        e = hipMalloc(&p, want);
+    }
+    if (e != hipSuccess) return fail(SLLM_E_HIP, "hipMalloc(%llu bytes) failed: %s", (unsigned long long)want, hipGetErrorString(e));
+    out->p = static_cast<uint8_t*>(p);
+    out->bytes = want;
+    return SLLM_OK;
+}
+
+void block_give(DeviceBlock* b) {
+    if (!b->p) return;
+    bool kept = false;
+    {
+        std::lock_guard<std::mutex> g(g_blocks_mu);
+        uint64_t held = 0;
+        size_t count = 0;
+        for (const DeviceBlock& i : g_idle_blocks)
+            if (i.device == b->device) {
+                held += i.bytes;
+                ++count;
+            }
+        if (count < kMaxIdleBlocks && b->bytes <= kMaxIdleBlockBytes && held <= kMaxIdleBlockBytes - b->bytes) {
+            g_idle_blocks.push_back(*b);
+            kept = true;
+        }
+    }
+    if (!kept) (void)hipFree(b->p);
+    *b = DeviceBlock{};
+}
+
+int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev_off, uint64_t dev_total,
+                            uint64_t dev_align, uint64_t staging_chunks, uint64_t chunk, DeviceLayout* out) {
+    DeviceLayout& l = *out;
+    l.n = ix.tensors.size();
+    l.total = ix.total;
+    l.dev_total = dev_total;
+    l.dev_align = dev_align;
+    l.tensors = ix.tensors.data();
+    l.h_dev = dev_off;
+    if (staging_chunks) {
+        uint64_t bytes;
+        if (!align_up(chunk, 256, &l.staging_stride) || !mul_ok(staging_chunks, l.staging_stride, &bytes))
+            return fail(SLLM_E_INVAL, "chunk size overflows");
+        SLLM_TRY(block_take(device, bytes, &l.stage));
+        l.staging = l.stage.p;
+    }
+    if (l.n == 0) return SLLM_OK;
+    // one block: o and d (n + 1 entries each), s, the plan
+    l.n_shift = ceil_div(dev_total, kPlanBytes);
+    SLLM_TRY(block_take(device, (3 * l.n + 2 + l.n_shift) * sizeof(uint64_t), &l.tables));
+    l.d_off = reinterpret_cast<uint64_t*>(l.tables.p);
+    l.d_dev = l.d_off + l.n + 1;
+    l.d_size = l.d_dev + l.n + 1;
+    l.d_shift = reinterpret_cast<int64_t*>(l.d_size + l.n);
+    const int32_t st = launch_tables(ix.tensors, ix.alignment, dev_align, l.d_size, l.d_off, l.d_dev, l.d_shift, l.n_shift, nullptr);
+    // loads run on other streams, and after a failed launch the block may go back
+    const hipError_t e = hipStreamSynchronize(nullptr);
+    if (st != SLLM_OK) return st;
+    SLLM_HIP(e);
+    return SLLM_OK;
+}
+
+void device_layout_free(DeviceLayout* l) {
+    block_give(&l->tables);
+    block_give(&l->stage);
+    *l = DeviceLayout{};
+}
+
+int32_t launch_scatter_window(const DeviceLayout& l, uint8_t* dst, const uint8_t* src, uint64_t x0, uint64_t x1,
+                              bool src_is_host, hipStream_t stream) {
+    ScatterArgs a{};
+    a.dst = dst;
+    a.base = src;
+    a.x0 = x0;
+    a.x1 = x1;
+    a.vec_ok = (reinterpret_cast<uintptr_t>(src) % 16 == 0) && (x0 % 16 == 0);
+    a.y0 = y_of(l, x0);
+    a.y1 = y_of(l, x1);
+    return launch(l, a, src_is_host, stream);
+}
+
+int32_t launch_scatter_run(const DeviceLayout& l, uint8_t* dst, const uint8_t* const* srcs, uint64_t k0, uint32_t m,
+                           uint64_t chunk, hipStream_t stream) {
+    if (m == 0) return SLLM_OK;
+    if (m > kScatterBatch || chunk == 0) return fail(SLLM_E_INVAL, "scatter run: bad size");
+    if (k0 >= ceil_div(l.total, chunk) || m > ceil_div(l.total, chunk) - k0)
+        return fail(SLLM_E_INVAL, "scatter run: chunks past the end of the image");
+    ScatterArgs a{};
+    a.dst = dst;
+    a.chunk = chunk;
+    a.run_n = m;
+    a.run_k0 = k0;
+    bool aligned = chunk % 16 == 0;
+    for (uint32_t j = 0; j < m; ++j) {
+        a.run_src[j] = srcs[j];
+        aligned = aligned && reinterpret_cast<uintptr_t>(srcs[j]) % 16 == 0;
+    }
+    a.vec_ok = aligned;
+    a.x0 = k0 * chunk;
+    a.x1 = std::min((k0 + m) * chunk, l.total);
+    a.y0 = y_of(l, a.x0);
+    a.y1 = y_of(l, a.x1);
+    return launch(l, a, /*src_is_host=*/true, stream);
+}
+
+int32_t launch_scatter_table(const DeviceLayout& l, uint8_t* dst, const uint8_t* const* table, uint64_t chunk,
+                             hipStream_t stream) {
+    ScatterArgs a{};
+    a.dst = dst;
+    a.table = table;
+    a.chunk = chunk;
+    a.vec_ok = chunk % 16 == 0;
+    a.y0 = 0;
+    a.y1 = l.dev_total;
+    return launch(l, a, /*src_is_host=*/true, stream);
+}
+
+}  // namespace sllm
+
+// ---------------------------------------------------------------------------
+// Allocation-free repack
+// ---------------------------------------------------------------------------
+
+// The device memory of the allocation-free repack: the size table, the two
+// scanned offset tables and one window of K2's plan (layout in
+// device_layout.hpp).  Every device holds its own copy from the library's
+// first kernel launch on it until the process ends.  Host code reaches a
+// device's copy only through the address hipGetSymbolAddress returns with
+// that device current; the name itself is not a device address on the host.
+static __device__ __align__(256) uint8_t scratch[sllm::kNoAllocScratchBytes];
+
+namespace sllm {
+
+namespace {
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
