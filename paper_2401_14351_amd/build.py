@@ -1,5 +1,6 @@
 """Build ``libsllm.so`` in-tree: the C++ host runtime and the gfx950 HIP kernels
-behind the C ABI declared in ``include/sllm.h``.
+behind the C ABI declared in ``include/sllm.h``; and ``_views.so``, the Python
+binding's native view builder (the only part that knows torch).
 
 Run ``python -m paper_2401_14351_amd.build`` (or ``__graft_entry__.build()``).
 """
@@ -18,6 +19,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsllm.so")
+VIEWS_SRC = os.path.join(PKG, "pyext", "views.cpp")
+VIEWS = os.path.join(PKG, "_views.so")
 ARCH = "gfx950"
 
 # Every HIP compile leaves packed-FP32 instructions out of the generated code.
@@ -52,8 +55,21 @@ def _run(cmd, verbose):
         print(out, flush=True)
 
 
+def views_command(out: str):
+    """The compiler call that makes the view builder for this interpreter and its torch."""
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(os.path.abspath(torch.__file__))
+    inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include")]
+    return [_cxx(), "-shared", "-O2", "-fPIC", "-std=c++17", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            f"-I{INCLUDE}", *[a for i in inc for a in ("-isystem", i)], f"-I{sysconfig.get_paths()['include']}", VIEWS_SRC,
+            "-o", out, f"-L{os.path.join(base, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link ``libsllm.so``; return its path."""
+    """Compile every source, link ``libsllm.so`` and ``_views.so``; return the former's path."""
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = []
     for src in sources():
@@ -63,12 +79,15 @@ def build(verbose: bool = False) -> str:
         else:
             cmd = [_cxx(), "-c", *COMMON, *HOST_FLAGS, src, "-o", obj]
         jobs.append((cmd, obj))
+    views_tmp = VIEWS + ".tmp"
+    jobs.insert(0, (views_command(views_tmp), None))  # the longest one first
     workers = max(1, min(len(jobs), os.cpu_count() or 1, 16))
     with ThreadPoolExecutor(workers) as ex:
         list(ex.map(lambda j: _run(j[0], verbose), jobs))
     tmp = LIB + ".tmp"
-    _run([_hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", *[o for _, o in jobs], "-o", tmp, "-lpthread"], verbose)
+    _run([_hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", *[o for _, o in jobs if o], "-o", tmp, "-lpthread"], verbose)
     os.replace(tmp, LIB)
+    os.replace(views_tmp, VIEWS)
     return LIB
 
 

@@ -1,0 +1,76 @@
+"""The native view builder against binding.views: the same names in the same
+order, and each view the same slice of the same storage with the same dtype,
+sizes, strides and relation to the buffer, for file layouts, device layouts
+and buffers that start inside a larger allocation."""
+
+import os
+
+import pytest
+import torch
+
+from paper_2401_14351_amd import binding, synth
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("libsllm.so not built")
+    return binding.lib()
+
+
+def same(a, b):
+    assert list(a) == list(b)
+    for name in a:
+        x, y = a[name], b[name]
+        assert (x.dtype, x.shape, x.stride(), x.storage_offset()) == (y.dtype, y.shape, y.stride(), y.storage_offset()), name
+        assert x.untyped_storage().data_ptr() == y.untyped_storage().data_ptr(), name
+        assert x.is_inference() == y.is_inference() and x.requires_grad == y.requires_grad, name
+        assert (x._base is None) == (y._base is None), name
+        assert x.is_inference() or x._version == y._version, name
+
+
+@pytest.mark.parametrize("A,A2", [(1, 0), (2, 0), (16, 0), (4096, 256), (1, 16)])
+@pytest.mark.parametrize("start", [0, 1, 2, 4, 48])
+def test_same_as_python(L, tmp_path, A, A2, start):
+    spec = synth.tiny(51, n=60, alignment=A, max_bytes=4000)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), A)
+    with binding.Checkpoint(str(tmp_path), index_only=True, dev_alignment=A2) as ck:
+        buf = torch.zeros(start + ck.total_bytes + 7, dtype=torch.uint8)[start:]
+        same(ck._views(buf, ck._table()), binding.views(buf, ck.tensors()))
+        with torch.inference_mode():
+            fresh = torch.zeros(ck.total_bytes, dtype=torch.uint8)
+            same(ck._views(fresh, ck._table()), binding.views(fresh, ck.tensors()))
+        got = ck._views(buf, ck._table())
+        next(v for v in got.values() if v.numel()).fill_(1)  # views share the buffer's bytes and its version
+        assert buf.any() and buf._version == 1
+
+
+def test_refuses_what_python_refuses(L, tmp_path):
+    spec = synth.tiny(52, n=10, alignment=16)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
+    with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+        for bad in (torch.zeros(4096, dtype=torch.float32), torch.zeros(64, 64, dtype=torch.uint8),
+                    torch.zeros(8192, dtype=torch.uint8)[::2]):
+            with pytest.raises(ValueError):
+                ck._views(bad, ck._table())
+        short = torch.zeros(8, dtype=torch.uint8)
+        for build in (lambda: binding.views(short, ck.tensors()), lambda: ck._views(short, ck._table())):
+            with pytest.raises(RuntimeError):
+                build()
+
+
+def test_function_modes_see_the_calls(L, tmp_path):
+    spec = synth.tiny(53, n=6, alignment=16)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
+    calls = []
+
+    class Mode(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            calls.append(func)
+            return func(*args, **(kwargs or {}))
+
+    with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+        buf = torch.zeros(ck.total_bytes, dtype=torch.uint8)
+        with Mode():
+            ck._views(buf, ck._table())
+        assert torch.Tensor.as_strided in calls
