@@ -39,6 +39,7 @@ struct DeviceLayout {
     uint64_t n = 0;                 // tensors
     uint64_t total = 0;             // T: bytes of the partition image
     uint64_t dev_total = 0;         // T2: bytes of the device image
+    uint64_t align = 0;             // A
     uint64_t dev_align = 0;         // A2
     uint64_t* d_off = nullptr;      // device: o_i
     uint64_t* d_size = nullptr;     // device: s_i
@@ -53,7 +54,7 @@ struct DeviceLayout {
 };
 
 // K2 from HBM moves the device image in tiles of kTileBytes (one 16-byte
-// vector for each of kK2Lanes lanes), one per workgroup.  Its plan holds, for
+// vector for each of kK2Lanes lanes) or twice that, one per workgroup.  Its plan holds, for
 // each block of kPlanBytes, the shift o_m - d_m from a destination byte to its
 // partition byte when the block lies inside the data bytes of one tensor m,
 // or kMixedTile + m when it meets a boundary or padding and its first byte
@@ -62,7 +63,7 @@ struct DeviceLayout {
 constexpr uint32_t kK2Lanes = 512;
 constexpr uint64_t kTileBytes = (uint64_t)kK2Lanes * 16;
 constexpr uint64_t kPlanBytes = 16384;
-static_assert(kPlanBytes == 2 * kTileBytes, "a workgroup moves both tiles of a mixed block");
+static_assert(kPlanBytes == 2 * kTileBytes, "a tile of either size lies in one plan block");
 constexpr int64_t kMixedTile = INT64_MIN;
 constexpr int64_t kMixedEnd = INT64_MIN / 2;
 

@@ -4,13 +4,12 @@
 //     and align_up(s_i, A2), scanned on the device from sizes that travel as
 //     kernel arguments, about 2,000 tensors a launch, together with K2's plan.
 // K2  index-driven scatter from HBM (the repack of a file-layout image, and
-//     copy-engine loads staged in HBM): destination-driven, one 8 KiB tile of
-//     the device image per workgroup of 512 lanes, tiles in dispatch order.
+//     copy-engine loads staged in HBM): destination-driven, one 8 or 16 KiB
+//     tile of the device image per workgroup of 512 lanes, in dispatch order.
 //     The plan gives, per 16 KiB block of the device image, the shift from a
 //     destination byte to its partition byte when the block lies inside one
-//     tensor's data; such tiles copy with one 16-byte vector per lane after a
-//     single table load.  The waves of the other tiles start from the tensor
-//     the plan names.
+//     tensor's data; such tiles copy after a single table load.  The waves of
+//     the other tiles start from the tensor the plan names.
 // K1-scatter (mapped pinned host source): each workgroup walks a span of
 //     tiles, finds the tensors whose slots meet a tile (a forward search of
 //     d), stages those index entries in LDS and keeps them for the following
@@ -472,34 +471,53 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t x, uint32_t lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// The vector at destination byte y from partition byte xs + at, where xs is
-// the same for the whole wave, and so the shift.
-template <bool NT>
-__device__ __forceinline__ void copy16(const K2Args& a, uint64_t y, uint64_t xs, uint32_t at) {
-    const uint32_t r = (uint32_t)(xs & 15);
+// The calling wave's N KiB of the device image at yw, from partition byte xs
+// on: one tensor's data, so xs and the shift are the same for every lane.
+// False if that reads past the window; nothing is written then.
+template <bool NT, int N>
+__device__ __forceinline__ bool k2_straight(const K2Args& a, uint64_t yw, uint64_t xs) {
+    // aligned 16-byte source vectors spanning [xs, xs + N KiB)
+    const uint64_t xa0 = xs & ~15ull, xa1 = (xs + N * 1024 + 15) & ~15ull;
+    if (!a.vec_ok || xa0 < a.x0 || xa1 > a.x1) return false;
+    const uint32_t at = (threadIdx.x & 63) * 16, r = (uint32_t)(xs & 15);
     // partition byte x sits at base + (x - x0); base and x0 are 16-byte aligned
     const uint8_t* p = a.base + (xs - a.x0) + at - r;
-    st16<NT>(a.dst + y, r == 0 ? ld16(p) : funnel(ld16(p), ld16(p + 16), r));
+    uint8_t* q = a.dst + yw + at;
+    u32x4 lo[N], hi[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) lo[k] = ld16(p + k * 1024);
+    if (r) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) hi[k] = ld16(p + k * 1024 + 16);
+#pragma unroll
+        for (int k = 0; k < N; ++k) lo[k] = funnel(lo[k], hi[k], r);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) st16<NT>(q + k * 1024, lo[k]);
+    return true;
 }
 
-// The calling wave's kilobyte of a tile of K2 that does not lie inside one
-// tensor's data: a boundary, padding, a window edge.  `w` is a tensor whose
-// slot starts at or before the tile.  The wave loads the index entries of 64
-// tensors from w on in one go, one per lane, and finds by ballot which of
-// them own its bytes; those, mostly one or two, go round the wave by scalar
-// lane reads and every lane keeps the last that starts at or before its
-// vector.  Only a wave that meets (or follows, within its plan block) more
-// than 64 tensors loads another 64.
-template <bool NT>
-__device__ __forceinline__ void k2_mixed(const K2Args& a, uint64_t yt, uint64_t w) {
+// The calling wave's N KiB at yw where they meet a boundary, padding or a
+// window edge, or their plan block does.  `w` is a tensor whose slot starts at
+// or before yw.  The wave loads the index entries of 64 tensors from w on in
+// one go, one per lane, and finds by ballot which of them own its bytes.
+// Where that is one tensor and its data cover them all, the wave copies
+// straight.  Else the owners, mostly two, go round the wave by scalar lane
+// reads and every lane keeps, for each of its N vectors, the last that starts
+// at or before it.  Only a wave that meets (or follows, within its plan block)
+// more than 64 tensors loads another 64.  What bounds it is the chain of the
+// plan entry, the index entries and the data, and the vector instructions, 4
+// cycles each for a wave; hence the one load of entries, the scalar case and
+// no LDS or barrier.
+template <bool NT, int N>
+__device__ __forceinline__ void k2_mixed(const K2Args& a, uint64_t yw, uint64_t w) {
     const Src<kWindow, K2Args> src{a};
     const uint32_t lane = threadIdx.x & 63;
-    const uint64_t yw = yt + 1024 * (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t lo = yw > a.y0 ? yw : a.y0;
-    const uint64_t hi = yw + 1024 < a.y1 ? yw + 1024 : a.y1;
+    const uint64_t hi = yw + N * 1024 < a.y1 ? yw + N * 1024 : a.y1;
     if (lo >= hi) return;
-    const uint64_t y = yw + lane * 16;
-    uint64_t dm = 0, om = 0, sm = 0;
+    const uint64_t y = yw + lane * 16;  // the lane's first vector; the others 1 KiB apart
+    uint64_t dm[N] = {}, om[N] = {}, sm[N] = {};
     for (;;) {
         const uint64_t i = w + lane;
         const bool in = i < a.n;
@@ -507,79 +525,92 @@ __device__ __forceinline__ void k2_mixed(const K2Args& a, uint64_t yt, uint64_t 
         const uint64_t next = w + 64 < a.n ? a.dev[w + 64] : ~0ull;  // start of the first slot past these
         const uint32_t before = __popcll(__ballot(d <= lo)), last = __popcll(__ballot(d < hi));
         const uint32_t first = before ? before - 1 : 0;
-        if (last == first + 1 && next >= hi && hi - lo == 1024) {
+        if (last == first + 1 && next >= hi && hi - lo == N * 1024) {
             const uint64_t dk = readlane64(d, first);
-            if (dk <= lo && hi <= dk + readlane64(s, first)) {
-                const uint64_t xs = readlane64(o, first) + (lo - dk);
-                if (src.vectors_ok(xs & ~15ull, 1040)) {
-                    copy16<NT>(a, y, xs, lane * 16);
-                    return;
-                }
-            }
+            if (dk <= lo && hi <= dk + readlane64(s, first) &&
+                k2_straight<NT, N>(a, yw, readlane64(o, first) + (lo - dk)))
+                return;
         }
         for (uint32_t k = first; k < last; ++k) {
             const uint64_t dk = readlane64(d, k), ok = readlane64(o, k), sk = readlane64(s, k);
-            if (y >= dk) {
-                dm = dk;
-                om = ok;
-                sm = sk;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                if (y + j * 1024 >= dk) {
+                    dm[j] = dk;
+                    om[j] = ok;
+                    sm[j] = sk;
+                }
             }
         }
         if (next >= hi) break;
         w += 64;
     }
-    if (y + 16 <= lo || y >= hi) return;
-    const uint64_t r = y - dm;                                                   // byte of the slot
-    const uint32_t dn = sm > r ? (sm - r < 16 ? (uint32_t)(sm - r) : 16u) : 0u;  // data bytes in the vector
-    const uint64_t x = om + r;                                                   // source of its first byte
-    const bool whole = y >= lo && y + 16 <= hi;                                  // entirely ours to write
-    u32x4 v = {0, 0, 0, 0};
-    if (dn) {
-        const uint64_t xa = x & ~15ull;
-        const uint32_t sh = (uint32_t)(x & 15);
-        const bool two = sh + dn > 16;  // the data span two aligned source vectors
-        if (whole && src.vectors_ok(xa, two ? 32 : 16)) {
-            const u32x4 v0 = ld16(src.at(xa));
-            v = keep_bytes(funnel_lanes(v0, two ? ld16(src.at(xa + 16)) : v0, sh), dn);
-        } else {
-            v = bytes_vector(src, y, lo, hi, x, dn);
+    struct Vec {
+        uint64_t x;   // source of its first byte
+        uint32_t dn;  // data bytes in it
+        bool whole;   // entirely ours to write
+        bool fast;    // its source vectors v0 and v1 could be loaded whole
+        u32x4 v0, v1;
+    } vec[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {  // every load in flight before the first is used
+        const uint64_t yj = y + j * 1024, r = yj - dm[j];  // byte of the slot
+        Vec& v = vec[j];
+        v.dn = sm[j] > r ? (sm[j] - r < 16 ? (uint32_t)(sm[j] - r) : 16u) : 0u;
+        v.x = om[j] + r;
+        v.whole = yj >= lo && yj + 16 <= hi;
+        const uint64_t xa = v.x & ~15ull;
+        const bool two = (v.x & 15) + v.dn > 16;  // the data span two aligned source vectors
+        v.fast = v.dn && v.whole && src.vectors_ok(xa, two ? 32 : 16);
+        v.v0 = v.v1 = u32x4{0, 0, 0, 0};
+        if (v.fast) {
+            v.v0 = ld16(src.at(xa));
+            if (two) v.v1 = ld16(src.at(xa + 16));
         }
     }
-    put_vector<NT>(a.dst, y, lo, hi, whole, v);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const uint64_t yj = y + j * 1024;
+        if (yj + 16 <= lo || yj >= hi) continue;
+        const Vec& v = vec[j];
+        u32x4 d = {0, 0, 0, 0};
+        if (v.fast) d = keep_bytes(funnel_lanes(v.v0, v.v1, (uint32_t)(v.x & 15)), v.dn);
+        else if (v.dn) d = bytes_vector(src, yj, lo, hi, v.x, v.dn);
+        put_vector<NT>(a.dst, yj, lo, hi, v.whole, d);
+    }
 }
 
-// K2 from HBM: one kTileBytes destination tile per workgroup of kK2Lanes
-// lanes, one vector per lane, tiles in dispatch order, so the workgroups in
-// flight sweep a contiguous window of both images (HBM serves that order
-// best).  A tile whose plan block lies inside one tensor's data, and whose
-// source bytes all lie in the window, copies straight from source byte
-// y + shift: one table load, then the data loads.  The waves of every other
-// tile take k2_mixed, from the tensor the plan entry names.
+// K2 from HBM: one destination tile of 8 N KiB per workgroup of kK2Lanes
+// lanes, N KiB a wave, tiles in dispatch order, so the workgroups in flight
+// sweep a contiguous window of both images (HBM serves that order best).  A
+// wave whose plan block lies inside one tensor's data, and whose source bytes
+// all lie in the window, copies straight from source byte y + shift: one table
+// load, then the data loads.  Every other wave goes from the tensor the plan
+// entry names.
 //
 // Four workgroups fit a CU, and the copy needs all four.  With more than 80
 // SGPRs a wave (the hardware takes them in steps of 16 and keeps 16 back) only
 // seven waves fit a SIMD, so three workgroups a CU: a 2.1 GB repack of straight
 // tiles took 680 us with 91 SGPRs and 646 us (6.5 TB/s) with 62 to 78.
-template <bool NT>
+//
+// N = 2 halves the chains per byte and so is for layouts whose blocks mostly
+// meet boundaries (k2_two_kib); copying straight it loses, 721 against 645 us
+// on those 2.1 GB.  20,000 tensors of 256 B to 64 KiB, 239 MB packed densely,
+// into A2 = 256: 184 us when one lane searched d and the workgroup staged the
+// entries in LDS, 98 with N = 1 and 83 (5.8 TB/s) with N = 2; N = 4 takes 92,
+// and two kilobytes in a workgroup whose neighbour then ends at once 120.
+template <bool NT, int N>
 __global__ __launch_bounds__(kK2Lanes) __attribute__((amdgpu_num_sgpr(80))) void k2_tiles(K2Args a) {
-    const uint64_t t = a.tile0 + blockIdx.x;
-    const uint64_t yt = t * kTileBytes;
+    constexpr uint64_t kTile = N * kTileBytes;
+    const uint64_t yt = (a.tile0 + blockIdx.x) * kTile;
+    const uint64_t yw = yt + N * 1024 * (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t sh = a.shift[yt / kPlanBytes - a.plan0];
     if (sh < kMixedEnd) {
-        k2_mixed<NT>(a, yt, (uint64_t)(sh - kMixedTile));
-        return;
+        k2_mixed<NT, N>(a, yw, (uint64_t)(sh - kMixedTile));
+    } else if (yw < a.y0 || yw + N * 1024 > a.y1 || !k2_straight<NT, N>(a, yw, yw + (uint64_t)sh)) {
+        // a straight block cut by the window's edge names no tensor: search for it
+        k2_mixed<NT, N>(a, yw, owner_global(a.dev, 0, a.n - 1, yw));
     }
-    if (yt >= a.y0 && yt + kTileBytes <= a.y1) {
-        const uint64_t xs = yt + (uint64_t)sh;  // source of the tile's first byte
-        // aligned 16-byte source vectors spanning [xs, xs + S)
-        const uint64_t xa0 = xs & ~15ull, xa1 = (xs + kTileBytes + 15) & ~15ull;
-        if (a.vec_ok && xa0 >= a.x0 && xa1 <= a.x1) {
-            copy16<NT>(a, yt + threadIdx.x * 16, xs, threadIdx.x * 16);
-            return;
-        }
-    }
-    // a straight block cut by the window's edge names no tensor: search for it
-    k2_mixed<NT>(a, yt, owner_global(a.dev, 0, a.n - 1, yt));
 }
 
 // K2's plan for destination blocks p0 .. p0 + n_blocks - 1: shift[p - p0] =
@@ -614,6 +645,17 @@ uint64_t y_of(const DeviceLayout& l, uint64_t x) {
     return l.h_dev[t - l.tensors] + (x > t->offset ? x - t->offset : 0);
 }
 
+// Whether K2 moves 2 KiB a wave (k2_tiles): where most plan blocks (16 KiB)
+// meet a boundary, so by the mean slot.  Measured, 1 against 2 KiB a wave:
+// every shift a multiple of 16, mean slots of 22 KiB 181 / 171 us, 39 KiB
+// 303 / 317, 69 KiB 428 / 471; through the byte funnel, which the second
+// vector in flight helps too, 21 KiB 191 / 170, 37 KiB 313 / 293, 68 KiB
+// 441 / 443.
+bool k2_two_kib(const DeviceLayout& l) {
+    const uint64_t mean = l.align % 16 == 0 ? 24 << 10 : 48 << 10;
+    return l.dev_total / mean <= l.n;
+}
+
 // Launch shape, read at every launch so that one process can compare shapes:
 // SLLM_K2_NT (streaming stores) and SLLM_K2_MAX_GRID (workgroups a launch)
 // for HBM sources; SLLM_K2_UNROLL (4 or 8 vectors per lane) and
@@ -644,16 +686,18 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
         k.shift = l.d_shift;
         k.plan0 = plan0;
         k.vec_ok = a.vec_ok;
-        const uint64_t t_end = ceil_div(a.y1, kTileBytes);
+        const bool two = k2_two_kib(l);
+        const uint64_t tile = two ? 2 * kTileBytes : kTileBytes;
+        const uint64_t t_end = ceil_div(a.y1, tile);
         // at most 2^31 lanes a launch (SLLM_K2_MAX_GRID lowers it, to exercise
         // the split on small images)
         constexpr uint64_t kMaxGrid = (1ull << 31) / kK2Lanes;
         const uint64_t max_grid = std::max<uint64_t>(1, std::min<uint64_t>(kMaxGrid, env_uint("SLLM_K2_MAX_GRID", kMaxGrid)));
-        for (uint64_t t0 = a.y0 / kTileBytes; t0 < t_end; t0 += max_grid) {
+        for (uint64_t t0 = a.y0 / tile; t0 < t_end; t0 += max_grid) {
             k.tile0 = t0;
-            const dim3 grid((uint32_t)std::min(max_grid, t_end - t0));
-            if (nt) k2_tiles<true><<<grid, dim3(kK2Lanes), 0, stream>>>(k);
-            else k2_tiles<false><<<grid, dim3(kK2Lanes), 0, stream>>>(k);
+            const dim3 grid((uint32_t)std::min(max_grid, t_end - t0)), block(kK2Lanes);
+            if (two) nt ? k2_tiles<true, 2><<<grid, block, 0, stream>>>(k) : k2_tiles<false, 2><<<grid, block, 0, stream>>>(k);
+            else nt ? k2_tiles<true, 1><<<grid, block, 0, stream>>>(k) : k2_tiles<false, 1><<<grid, block, 0, stream>>>(k);
             SLLM_HIP(hipGetLastError());
         }
         return SLLM_OK;
@@ -827,6 +871,7 @@ int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev
     l.n = ix.tensors.size();
     l.total = ix.total;
     l.dev_total = dev_total;
+    l.align = ix.alignment;
     l.dev_align = dev_align;
     l.tensors = ix.tensors.data();
     l.h_dev = dev_off;
@@ -970,6 +1015,7 @@ int32_t repack_noalloc(const IndexData& ix, int device, uint64_t dev_align, uint
     l.n = n;
     l.total = ix.total;
     l.dev_total = dev_total;
+    l.align = ix.alignment;
     l.dev_align = dev_align;
     l.d_off = d_off;
     l.d_size = d_size;
