@@ -78,8 +78,11 @@ void device_layout_free(DeviceLayout* l);
 
 // Move partition window [x0, x1), held contiguously at `src` (device memory,
 // or a device-visible mapping of pinned host memory), into the device image.
+// With `end` (device memory sources only) that event completes with the last
+// kernel, by the kernel's own completion signal: no packet of its own follows
+// on the stream, and no system-scope fence.
 int32_t launch_scatter_window(const DeviceLayout& l, uint8_t* dst, const uint8_t* src, uint64_t x0, uint64_t x1,
-                              bool src_is_host, hipStream_t stream);
+                              bool src_is_host, hipStream_t stream, hipEvent_t end = nullptr);
 
 // Move the whole partition, held in pinned chunks listed by `table` (device
 // array; chunk k holds partition bytes [kC, kC + C)), into the device image.

@@ -18,6 +18,7 @@
 //     when source and destination agree mod 16, two aligned loads and a byte
 //     funnel shift when they do not, zeros for padding.  Only vectors cut by
 //     the window's first or last destination byte are written byte by byte.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -661,7 +662,8 @@ bool k2_two_kib(const DeviceLayout& l) {
 // for HBM sources; SLLM_K2_UNROLL (4 or 8 vectors per lane) and
 // SLLM_K1_BLOCKS / SLLM_K1_STREAM_BLOCKS (grid of a launch that moves the
 // whole image / part of it, as for K1) for host sources.
-int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream_t stream, uint64_t plan0 = 0) {
+int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream_t stream, uint64_t plan0 = 0,
+               hipEvent_t end = nullptr) {
     a.off = l.d_off;
     a.size = l.d_size;
     a.dev = l.d_dev;
@@ -696,8 +698,9 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
         for (uint64_t t0 = a.y0 / tile; t0 < t_end; t0 += max_grid) {
             k.tile0 = t0;
             const dim3 grid((uint32_t)std::min(max_grid, t_end - t0)), block(kK2Lanes);
-            if (two) nt ? k2_tiles<true, 2><<<grid, block, 0, stream>>>(k) : k2_tiles<false, 2><<<grid, block, 0, stream>>>(k);
-            else nt ? k2_tiles<true, 1><<<grid, block, 0, stream>>>(k) : k2_tiles<false, 1><<<grid, block, 0, stream>>>(k);
+            const auto kernel = two ? (nt ? k2_tiles<true, 2> : k2_tiles<false, 2>) : (nt ? k2_tiles<true, 1> : k2_tiles<false, 1>);
+            if (end && t_end - t0 <= max_grid) hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, nullptr, end, 0, k);
+            else kernel<<<grid, block, 0, stream>>>(k);
             SLLM_HIP(hipGetLastError());
         }
         return SLLM_OK;
@@ -905,7 +908,7 @@ void device_layout_free(DeviceLayout* l) {
 }
 
 int32_t launch_scatter_window(const DeviceLayout& l, uint8_t* dst, const uint8_t* src, uint64_t x0, uint64_t x1,
-                              bool src_is_host, hipStream_t stream) {
+                              bool src_is_host, hipStream_t stream, hipEvent_t end) {
     ScatterArgs a{};
     a.dst = dst;
     a.base = src;
@@ -914,7 +917,7 @@ int32_t launch_scatter_window(const DeviceLayout& l, uint8_t* dst, const uint8_t
     a.vec_ok = (reinterpret_cast<uintptr_t>(src) % 16 == 0) && (x0 % 16 == 0);
     a.y0 = y_of(l, x0);
     a.y1 = y_of(l, x1);
-    return launch(l, a, src_is_host, stream);
+    return launch(l, a, src_is_host, stream, 0, end);
 }
 
 int32_t launch_scatter_run(const DeviceLayout& l, uint8_t* dst, const uint8_t* const* srcs, uint64_t k0, uint32_t m,

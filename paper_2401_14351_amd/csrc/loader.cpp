@@ -68,6 +68,7 @@ struct sllm_ckpt {
     // reads go back: the events of loads and repacks that may still run, and
     // completed ones for reuse
     mutable std::vector<hipEvent_t> end_evs, end_free;
+    mutable size_t end_look = 0;    // the next of end_evs to look at
     bool timed = false;             // t0/t1 bracket the last load
     DeviceLayout layout;            // device tables for A2 layouts
     bool keep = false;              // SLLM_OPEN_CACHE: chunk k streams into slot k, kept afterwards
@@ -198,29 +199,40 @@ int32_t ensure_streams(sllm_ckpt* h) {
     return SLLM_OK;
 }
 
-// Record an end event on `s` after a load's or repack's work (events of
-// earlier ones that have completed are reused).
-int32_t mark_end(const sllm_ckpt* h, hipStream_t s) {
-    for (size_t i = 0; i < h->end_evs.size();) {
-        if (hipEventQuery(h->end_evs[i]) == hipSuccess) {
-            h->end_free.push_back(h->end_evs[i]);
-            h->end_evs[i] = h->end_evs.back();
-            h->end_evs.pop_back();
-        } else {
-            ++i;
-        }
+// An event for the end of a load or repack, taken from those whose work has
+// completed, else new; it is on h->end_free's back until the caller moves it.
+// Each call looks at a few of the outstanding events, which frees them faster
+// than calls add them without a query for every one in flight.
+int32_t free_end_event(const sllm_ckpt* h, hipEvent_t* out) {
+    for (int look = 0; look < 4 && !h->end_evs.empty(); ++look) {
+        const size_t i = h->end_look++ % h->end_evs.size();
+        if (hipEventQuery(h->end_evs[i]) != hipSuccess) continue;
+        h->end_free.push_back(h->end_evs[i]);
+        h->end_evs[i] = h->end_evs.back();
+        h->end_evs.pop_back();
     }
     (void)hipGetLastError();  // a query of pending work is not an error
-    hipEvent_t e = nullptr;
-    if (!h->end_free.empty()) {
-        e = h->end_free.back();
-    } else {
+    if (h->end_free.empty()) {
+        hipEvent_t e = nullptr;
         SLLM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         h->end_free.push_back(e);
     }
-    SLLM_HIP(hipEventRecord(e, s));
+    *out = h->end_free.back();
+    return SLLM_OK;
+}
+
+// The event free_end_event gave will complete with the work now queued.
+void use_end_event(const sllm_ckpt* h) {
+    h->end_evs.push_back(h->end_free.back());
     h->end_free.pop_back();
-    h->end_evs.push_back(e);
+}
+
+// Record an end event on `s` after a load's or repack's work.
+int32_t mark_end(const sllm_ckpt* h, hipStream_t s) {
+    hipEvent_t e = nullptr;
+    SLLM_TRY(free_end_event(h, &e));
+    SLLM_HIP(hipEventRecord(e, s));
+    use_end_event(h);
     return SLLM_OK;
 }
 
@@ -806,9 +818,23 @@ extern "C" int32_t sllm_repack(const sllm_ckpt* h, const void* src_dev, uint64_t
     SLLM_TRY(check_device_range(dst_dev, h->dev_total, h->device, "destination"));
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* dst = static_cast<uint8_t*>(dst_dev);
-    int32_t st = launch_scatter_window(h->layout, dst, static_cast<const uint8_t*>(src_dev), 0, h->ix.total,
-                                       /*src_is_host=*/false, s);
-    if (st == SLLM_OK) st = mark_end(h, s);
+    const uint8_t* src = static_cast<const uint8_t*>(src_dev);
+    // The end event rides on the kernel: a recorded event is a packet of its own
+    // with a system-scope fence, 2.6 us on the stream after each repack (40 MB
+    // in and out: 10.4 -> 7.8 us a repack).  Under capture it is recorded.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    int32_t st;
+    if (eager) {
+        hipEvent_t end = nullptr;
+        SLLM_TRY(free_end_event(h, &end));
+        st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s, end);
+        if (st == SLLM_OK) use_end_event(h);
+    } else {
+        (void)hipGetLastError();
+        st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s);
+        if (st == SLLM_OK) st = mark_end(h, s);
+    }
     if (st != SLLM_OK) (void)hipStreamSynchronize(s);  // close could not wait for what was launched
     return st;
 } SLLM_CATCH_ALL

@@ -93,3 +93,63 @@ def test_close_waits_for_a_repack(torch_cuda, tmp_path):
     say("repack: stream idle after close:", idle)
     assert idle, "close returned while a repack still ran on the caller's stream"
     assert out.cpu().numpy().tobytes() == want
+
+
+@pytest.mark.parametrize("grid", [None, "997"])
+def test_close_waits_for_repacks_on_two_streams(torch_cuda, tmp_path, monkeypatch, grid):
+    """More repacks in flight than end events looked at per call, on two
+    streams, whole and split into several launches (the end rides on the last)."""
+    torch = torch_cuda
+    if grid:
+        monkeypatch.setenv("SLLM_K2_MAX_GRID", grid)
+    spec = synth.stress(n=400, max_bytes=1 << 20, seed=44)
+    tensors = [(t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))]
+    d = str(tmp_path / "two")
+    binding.convert(iter(tensors), d, 4096, 1 << 20)
+    index = oracle.make_index(tensors, 4096, 1 << 20)
+    image = bytes(oracle.partition_bytes(tensors, 4096)[:index.total_bytes])
+    want = bytes(oracle.repack(image, index, 256))
+    src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [torch.full((len(want),), 0xA5, dtype=torch.uint8, device="cuda:0") for _ in streams]
+    torch.cuda.synchronize()
+    ck = binding.Checkpoint(d, dev_alignment=256)
+    for i in range(60):
+        ck.repack(src, outs[i % 2], streams[i % 2])
+    ck.close()
+    assert all(s.query() for s in streams), "close returned while a repack still ran"
+    for o in outs:
+        assert o.cpu().numpy().tobytes() == want
+
+
+def test_repack_captured_in_a_graph(torch_cuda, tmp_path):
+    """sllm_repack under capture: recorded once, replayed with the handle open,
+    eager repacks and synchronizations between the replays."""
+    torch = torch_cuda
+    spec = synth.stress(n=60, max_bytes=256 << 10, seed=45)
+    tensors = [(t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))]
+    d = str(tmp_path / "cap")
+    binding.convert(iter(tensors), d, 4096, 1 << 20)
+    index = oracle.make_index(tensors, 4096, 1 << 20)
+    image = bytes(oracle.partition_bytes(tensors, 4096)[:index.total_bytes])
+    want = bytes(oracle.repack(image, index, 256))
+    src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+    out = torch.empty(len(want), dtype=torch.uint8, device="cuda:0")
+    other = torch.empty_like(out)
+    with binding.Checkpoint(d, dev_alignment=256) as ck:
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            ck.repack(src, out, side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            ck.repack(src, out, torch.cuda.current_stream())
+        for k in range(3):
+            out.fill_(0xA5)
+            ck.repack(src, other, torch.cuda.current_stream())
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert out.cpu().numpy().tobytes() == want, f"replay {k}"
+            assert other.cpu().numpy().tobytes() == want, f"eager {k}"
+        del g
