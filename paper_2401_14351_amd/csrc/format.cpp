@@ -285,6 +285,7 @@ int32_t decode_index(const void* data, size_t n, IndexData* out) {
     // each record takes at least 25 bytes, which bounds a sane count
     if (count > (n - kHeaderBytes) / 25) return fail(SLLM_E_FORMAT, "index tensor count %llu is impossible", (unsigned long long)count);
     ix.tensors.resize(count);
+    ix.sizes.resize(count);
     ix.names.reserve(n);  // the names fit in the index, so the buffer never moves
     NameSet names(ix);
     uint64_t padded_sum = 0;
@@ -311,6 +312,7 @@ int32_t decode_index(const void* data, size_t n, IndexData* out) {
             return fail(SLLM_E_FORMAT, "record '%s' truncated", name);
         if (check_tensor_meta(name, t.dtype, t.ndim, t.shape, t.nbytes) != SLLM_OK)
             return fail(SLLM_E_FORMAT, "record '%s': %s", name, sllm_last_error());
+        ix.sizes[i] = t.nbytes;
         if (!names.insert((uint32_t)i)) return fail(SLLM_E_FORMAT, "duplicate tensor name '%s'", name);
         // tensors packed in order: o_i is the end of the previous padded slot
         if (t.offset != padded_sum)

@@ -38,6 +38,7 @@ struct IndexData {
     uint64_t total = 0;       // T = sum align_up(s_i, A)
     uint64_t file_bytes = 0;  // F = align_up(T, 4096)
     std::vector<TensorRec> tensors;
+    std::vector<uint64_t> sizes;  // s_i of a decoded index (the records' nbytes, side by side)
     // every tensor's name followed by a NUL, in record order: one buffer for
     // all names instead of an allocation per name
     std::string names;

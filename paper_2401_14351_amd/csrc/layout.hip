@@ -52,6 +52,12 @@ __device__ __forceinline__ uint64_t dpp64(uint64_t x) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+__device__ __forceinline__ uint64_t readlane64(uint64_t x, uint32_t lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // inclusive scan across the 64 lanes of a wave: shifts by 1, 2, 4 and 8 inside
 // the rows of 16, then lane 15 of each row into the next and lane 31 into the
 // upper half.  Register moves, where shuffles by lane address go through LDS.
@@ -75,7 +81,7 @@ __device__ __forceinline__ int64_t plan_entry(uint64_t y, uint64_t dm, uint64_t 
 // arguments, and the plan entries (device_layout.hpp) of the blocks whose first
 // byte lies in the batch's slots.
 constexpr uint32_t kTableBatch = 2048;  // tensors a batch holds at most
-constexpr uint32_t kTableWords = 996;
+constexpr uint32_t kTableWords = 994;
 struct TableArgs {
     uint64_t *size, *off, *dev;  // the layout's tables
     int64_t* plan;               // entry of block p at plan[p - p0], for p in [p0, p0 + n_plan)
@@ -86,6 +92,7 @@ struct TableArgs {
     uint64_t base;               // s = base + (v << shift), v the tensor's `width` bits of `words`
     uint32_t m, width, shift;
     uint32_t last;               // the batch ends the index: o_n and d_n too
+    uint32_t spread;             // many plan blocks: they are spread over the grid
     uint32_t words[kTableWords];
 };
 static_assert(sizeof(TableArgs) <= 4096, "kernel arguments fit 4 KiB");
@@ -102,16 +109,26 @@ __device__ __forceinline__ uint64_t table_size(const TableArgs& a, uint32_t j) {
     return a.base + (v << a.shift);
 }
 
-// One workgroup decodes the sizes and scans both layouts' padded sizes (two
-// tensors a lane, a shuffle scan in each wave, the 16 wave totals through
-// LDS), leaves d, o and s in LDS and writes the batch's tables; every
-// workgroup of a larger grid repeats that and takes its share of the plan
-// blocks, each by bisection of d in LDS.  Batches do not wait for each
-// other's scan: the host passes where each starts.  All of it is latency, so
-// fewer launches count: 20,000 tensors of 256 B to 64 KiB need 11 launches of
-// these (16 bits a size, 5 us each), where 256 64-bit sizes a launch, a scan
-// kernel per layout and a plan kernel took 82 launches: the repack they
-// prepare went from 336 to 140 us.
+// At most this many plan blocks per tensor of a batch, on average, and one
+// workgroup writes them tensor by tensor.
+constexpr uint64_t kTableBlocksEach = 4;
+
+// One workgroup decodes the sizes, scans both layouts' padded sizes (two
+// tensors a lane, a scan in each wave, the 16 wave totals through LDS) and
+// writes the batch's tables.  Batches do not wait for each other's scan: the
+// host passes where each starts.  The plan follows in one of two ways: tensor
+// by tensor from the registers where the batch has few blocks (a.spread == 0,
+// one workgroup; a run of more than 8 blocks goes round the wave), else every
+// workgroup of a larger grid repeats the scan, leaves d, o and s in LDS and
+// takes its share of the blocks, each by bisection of d.
+//
+// All of it is latency, so fewer launches and shorter chains count: 20,000
+// tensors of 256 B to 64 KiB need 11 launches of these (16 bits a size), where
+// 256 64-bit sizes a launch, a scan kernel per layout and a plan kernel took
+// 82: the repack they prepare went from 336 to 139 us, and to 134 with the plan
+// from registers and no second barrier.  Of a launch's 5.3 us
+// by bisection, 2.0 were the launch and its arguments, 0.6 the sizes, 1.3 the
+// scans and 1.4 the plan.
 __global__ __launch_bounds__(1024) void k3_tables(TableArgs a) {
     __shared__ uint64_t s_dev[kTableBatch], s_off[kTableBatch], s_size[kTableBatch];
     __shared__ uint64_t tot_o[16], tot_d[16];
@@ -127,23 +144,12 @@ __global__ __launch_bounds__(1024) void k3_tables(TableArgs a) {
         tot_d[wave] = d_incl;
     }
     __syncthreads();
-    if (wave == 0) {
-        const uint64_t o = wave_scan(lane < 16 ? tot_o[lane] : 0), d = wave_scan(lane < 16 ? tot_d[lane] : 0);
-        if (lane < 16) {
-            tot_o[lane] = o;
-            tot_d[lane] = d;
-        }
-    }
-    __syncthreads();
-    const uint64_t o = a.o0 + (wave ? tot_o[wave - 1] : 0) + o_incl - o_both;
-    const uint64_t d = a.d0 + (wave ? tot_d[wave - 1] : 0) + d_incl - d_both;
-    const uint64_t o_end = a.o0 + tot_o[15], d_end = a.d0 + tot_d[15];
-    s_off[j0] = o;
-    s_dev[j0] = d;
-    s_size[j0] = s0;
-    s_off[j1] = o + o_first;
-    s_dev[j1] = d + d_first;
-    s_size[j1] = s1;
+    // every wave scans the 16 totals for itself
+    const uint64_t o_tot = wave_scan(lane < 16 ? tot_o[lane] : 0), d_tot = wave_scan(lane < 16 ? tot_d[lane] : 0);
+    const uint32_t w = __builtin_amdgcn_readfirstlane(wave);
+    const uint64_t o = a.o0 + (w ? readlane64(o_tot, w - 1) : 0) + o_incl - o_both;
+    const uint64_t d = a.d0 + (w ? readlane64(d_tot, w - 1) : 0) + d_incl - d_both;
+    const uint64_t o_end = a.o0 + readlane64(o_tot, 15), d_end = a.d0 + readlane64(d_tot, 15);
     if (blockIdx.x == 0) {
         if (j0 < a.m) {
             a.size[a.i0 + j0] = s0;
@@ -160,11 +166,37 @@ __global__ __launch_bounds__(1024) void k3_tables(TableArgs a) {
             a.dev[a.i0 + a.m] = d_end;
         }
     }
-    __syncthreads();
     // blocks p with d0 <= p * kPlanBytes < d_end, inside the plan's window
+    const uint64_t w_begin = a.p0, w_end = a.p0 + a.n_plan;
+    if (!a.spread) {
+        auto fill = [&](uint64_t dm, uint64_t slot, uint64_t om, uint64_t sm, uint64_t m) {
+            uint64_t p = (dm + kPlanBytes - 1) / kPlanBytes, p_end = (dm + slot + kPlanBytes - 1) / kPlanBytes;
+            if (p < w_begin) p = w_begin;
+            if (p_end > w_end) p_end = w_end;
+            const bool run = p_end > p && p_end - p > 8;
+            if (!run)
+                for (uint64_t b = p; b < p_end; ++b) a.plan[b - a.p0] = plan_entry(b * kPlanBytes, dm, om, sm, m);
+            for (uint64_t left = __ballot(run); left; left &= left - 1) {
+                const uint32_t k = __builtin_ctzll(left);
+                const uint64_t dk = readlane64(dm, k), ok = readlane64(om, k), sk = readlane64(sm, k), mk = readlane64(m, k);
+                const uint64_t pk = readlane64(p, k), ek = readlane64(p_end, k);
+                for (uint64_t b = pk + lane; b < ek; b += 64) a.plan[b - a.p0] = plan_entry(b * kPlanBytes, dk, ok, sk, mk);
+            }
+        };
+        fill(d, d_first, o, s0, a.i0 + j0);
+        fill(d + d_first, d_both - d_first, o + o_first, s1, a.i0 + j1);
+        return;
+    }
+    s_off[j0] = o;
+    s_dev[j0] = d;
+    s_size[j0] = s0;
+    s_off[j1] = o + o_first;
+    s_dev[j1] = d + d_first;
+    s_size[j1] = s1;
+    __syncthreads();
     uint64_t p = (a.d0 + kPlanBytes - 1) / kPlanBytes, p_end = (d_end + kPlanBytes - 1) / kPlanBytes;
-    if (p < a.p0) p = a.p0;
-    if (p_end > a.p0 + a.n_plan) p_end = a.p0 + a.n_plan;
+    if (p < w_begin) p = w_begin;
+    if (p_end > w_end) p_end = w_end;
     for (p += (uint64_t)blockIdx.x * 1024 + tid; p < p_end; p += (uint64_t)gridDim.x * 1024) {
         const uint64_t y = p * kPlanBytes;
         uint32_t l = 0, h = a.m - 1;  // d of the batch's first tensor <= y
@@ -466,12 +498,6 @@ __global__ __launch_bounds__(kThreads) void k_scatter(ScatterArgs a) {
     scatter_span<kThreads, U, NT, K>(a, stg, t_begin, t_end);
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t x, uint32_t lane) {
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 // The calling wave's N KiB of the device image at yw, from partition byte xs
 // on: one tensor's data, so xs and the shift are the same for every lane.
 // False if that reads past the window; nothing is written then.
@@ -726,46 +752,49 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
 
 namespace {
 
-// Fill a.words with the sizes of tensors i0 .. and return how many fit: the
-// sizes less the smallest of them, without the low zero bits they share, in as
-// many bits as the largest needs.
-uint32_t pack_sizes(const std::vector<TensorRec>& t, uint64_t i0, TableArgs* a) {
-    const uint64_t first = t[i0].nbytes, n = std::min<uint64_t>(kTableBatch, t.size() - i0);
-    uint64_t lo = first, hi = first, diff = 0;
-    uint32_t m = 0;
-    a->width = a->shift = 0;
-    a->base = first;
-    for (; m < n; ++m) {
-        const uint64_t s = t[i0 + m].nbytes;
-        const uint64_t l = std::min(lo, s), h = std::max(hi, s), df = diff | (s - first);
-        const uint32_t shift = df ? (uint32_t)__builtin_ctzll(df) : 0;
-        const uint32_t width = h == l ? 0 : 64 - (uint32_t)__builtin_clzll((h - l) >> shift);
-        if ((uint64_t)width * (m + 1) > kTableBits) break;
-        lo = l;
-        hi = h;
-        diff = df;
-        a->shift = shift;
-        a->width = width;
-        a->base = l;
+// Fill a.words with the first of the n sizes at s (at most kTableBatch of them)
+// and return how many fit: the sizes less the smallest of them, without the low
+// zero bits they share, in as many bits as the largest needs.
+uint32_t pack_sizes(const uint64_t* s, uint64_t n, TableArgs* a) {
+    uint64_t m = std::min<uint64_t>(kTableBatch, n);
+    uint64_t lo = s[0], hi = s[0], diff = 0;
+    for (uint64_t j = 1; j < m; ++j) {
+        lo = std::min(lo, s[j]);
+        hi = std::max(hi, s[j]);
+        diff |= s[j] - s[0];
     }
-    std::memset(a->words, 0, sizeof a->words);
-    if (a->width == 0) return m;
-    for (uint32_t j = 0; j < m; ++j) {
-        const uint64_t v = (t[i0 + j].nbytes - a->base) >> a->shift, bit = (uint64_t)j * a->width;
-        const uint32_t k = (uint32_t)(bit >> 5), sh = (uint32_t)(bit & 31);
-        const unsigned __int128 x = (unsigned __int128)v << sh;
-        a->words[k] |= (uint32_t)x;
-        a->words[k + 1] |= (uint32_t)(x >> 32);
-        a->words[k + 2] |= (uint32_t)(x >> 64);
+    const uint32_t shift = diff ? (uint32_t)__builtin_ctzll(diff) : 0;
+    const uint32_t width = hi == lo ? 0 : 64 - (uint32_t)__builtin_clzll((hi - lo) >> shift);
+    a->base = lo;
+    a->shift = shift;
+    a->width = width;
+    if (width == 0) return (uint32_t)m;
+    m = std::min(m, kTableBits / width);
+    uint64_t acc = 0;
+    uint32_t fill = 0;
+    uint32_t* w = a->words;
+    for (uint64_t j = 0; j < m; ++j) {
+        const uint64_t v = (s[j] - lo) >> shift;
+        acc |= v << fill;
+        if (fill + width >= 64) {
+            std::memcpy(w, &acc, 8);
+            w += 2;
+            acc = fill ? v >> (64 - fill) : 0;
+            fill = fill + width - 64;
+        } else {
+            fill += width;
+        }
     }
-    return m;
+    std::memcpy(w, &acc, 8);  // kTableBits leaves two words past the last value
+    return (uint32_t)m;
 }
 
-// Compute the tables of every tensor (file layout at alignment `align`, device
-// layout at `dev_align`) and the plan's first n_plan entries on `stream`.
-int32_t launch_tables(const std::vector<TensorRec>& t, uint64_t align, uint64_t dev_align, uint64_t* size, uint64_t* off,
+// Compute the tables of the n tensors of sizes s (file layout at alignment
+// `align`, device layout at `dev_align`) and the plan's first n_plan entries on
+// `stream`.
+int32_t launch_tables(const std::vector<uint64_t>& s, uint64_t align, uint64_t dev_align, uint64_t* size, uint64_t* off,
                       uint64_t* dev, int64_t* plan, uint64_t n_plan, hipStream_t stream) {
-    TableArgs a;
+    TableArgs a{};
     a.size = size;
     a.off = off;
     a.dev = dev;
@@ -774,19 +803,18 @@ int32_t launch_tables(const std::vector<TensorRec>& t, uint64_t align, uint64_t 
     a.n_plan = n_plan;
     a.align_o = align;
     a.align_d = dev_align;
-    a.o0 = a.d0 = 0;
-    for (a.i0 = 0; a.i0 < t.size(); a.i0 += a.m) {
-        a.m = pack_sizes(t, a.i0, &a);
-        a.last = a.i0 + a.m == t.size();
+    for (a.i0 = 0; a.i0 < s.size(); a.i0 += a.m) {
+        a.m = pack_sizes(s.data() + a.i0, s.size() - a.i0, &a);
+        a.last = a.i0 + a.m == s.size();
         uint64_t o = a.o0, d = a.d0;
         for (uint32_t j = 0; j < a.m; ++j) {  // both totals were checked against 64 bits before
-            const uint64_t s = t[a.i0 + j].nbytes;
-            o += (s + align - 1) & ~(align - 1);
-            d += (s + dev_align - 1) & ~(dev_align - 1);
+            o += (s[a.i0 + j] + align - 1) & ~(align - 1);
+            d += (s[a.i0 + j] + dev_align - 1) & ~(dev_align - 1);
         }
-        // a workgroup for each 1024 blocks of the plan
         const uint64_t blocks = std::min(ceil_div(d, kPlanBytes), n_plan) - std::min(a.d0 / kPlanBytes, n_plan);
-        const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(512, ceil_div(blocks, 1024)));
+        a.spread = blocks > kTableBlocksEach * a.m;
+        // spread: a workgroup for each 1024 blocks of the plan
+        const uint32_t grid = a.spread ? (uint32_t)std::min<uint64_t>(512, ceil_div(blocks, 1024)) : 1;
         k3_tables<<<dim3(grid), dim3(1024), 0, stream>>>(a);
         SLLM_HIP(hipGetLastError());
         a.o0 = o;
@@ -893,7 +921,7 @@ int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev
     l.d_dev = l.d_off + l.n + 1;
     l.d_size = l.d_dev + l.n + 1;
     l.d_shift = reinterpret_cast<int64_t*>(l.d_size + l.n);
-    const int32_t st = launch_tables(ix.tensors, ix.alignment, dev_align, l.d_size, l.d_off, l.d_dev, l.d_shift, l.n_shift, nullptr);
+    const int32_t st = launch_tables(ix.sizes, ix.alignment, dev_align, l.d_size, l.d_off, l.d_dev, l.d_shift, l.n_shift, nullptr);
     // loads run on other streams, and after a failed launch the block may go back
     const hipError_t e = hipStreamSynchronize(nullptr);
     if (st != SLLM_OK) return st;
@@ -1030,7 +1058,7 @@ int32_t repack_noalloc(const IndexData& ix, int device, uint64_t dev_align, uint
     for (uint64_t p0 = 0; p0 < n_blocks; p0 += window) {
         const uint64_t nb = std::min(window, n_blocks - p0);
         if (p0 == 0) {
-            SLLM_TRY(launch_tables(ix.tensors, ix.alignment, dev_align, d_size, d_off, d_dev, plan, nb, stream));
+            SLLM_TRY(launch_tables(ix.sizes, ix.alignment, dev_align, d_size, d_off, d_dev, plan, nb, stream));
         } else {
             const uint64_t blocks = std::min<uint64_t>(ceil_div(nb, 256), 4096);
             k3_tile_shift<<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(d_dev, d_off, d_size, n, p0, nb, plan);

@@ -628,9 +628,7 @@ extern "C" int32_t sllm_open(const char* dir, const sllm_open_opts* opts, sllm_c
     const size_t nt = h->ix.tensors.size();
     h->dev_off.resize(nt);
     if (h->dev_align) {
-        std::vector<uint64_t> sizes(nt);
-        for (size_t i = 0; i < nt; ++i) sizes[i] = h->ix.tensors[i].nbytes;
-        st = plan_layout(sizes.data(), nt, h->dev_align, h->dev_off.data(), &h->dev_total);
+        st = plan_layout(h->ix.sizes.data(), nt, h->dev_align, h->dev_off.data(), &h->dev_total);
         if (st != SLLM_OK) return bail(st);
     } else {
         for (size_t i = 0; i < nt; ++i) h->dev_off[i] = h->ix.tensors[i].offset;
@@ -851,11 +849,20 @@ extern "C" int32_t sllm_repack_noalloc(const sllm_ckpt* h, uint64_t dev_alignmen
     if (n > kNoAllocMaxTensors)
         return fail(SLLM_E_RANGE, "%llu tensors exceed the %llu the allocation-free repack holds", (unsigned long long)n,
                     (unsigned long long)kNoAllocMaxTensors);
-    uint64_t t2 = 0;  // T2 = sum align_up(s_i, A2), without a host table
-    for (const TensorRec& t : h->ix.tensors) {
-        uint64_t padded = 0;
-        if (!align_up(t.nbytes, a2, &padded) || !add_ok(t2, padded, &t2))
-            return fail(SLLM_E_RANGE, "the device layout overflows 64 bits");
+    // T2 = sum align_up(s_i, A2); at most 2^16 sizes, so no sum of padded sizes
+    // below 2^47 overflows and one plain pass decides whether to check each step
+    uint64_t t2 = 0, bits = a2;
+    for (const uint64_t s : h->ix.sizes) {
+        bits |= s;
+        t2 += (s + a2 - 1) & ~(a2 - 1);
+    }
+    if (bits >> 46) {
+        t2 = 0;
+        for (const uint64_t s : h->ix.sizes) {
+            uint64_t padded = 0;
+            if (!align_up(s, a2, &padded) || !add_ok(t2, padded, &t2))
+                return fail(SLLM_E_RANGE, "the device layout overflows 64 bits");
+        }
     }
     const uint64_t total = h->ix.total;
     if (src_bytes < total || dst_bytes < t2)
