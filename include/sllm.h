@@ -71,7 +71,8 @@
  *   SLLM_K1_BLOCKS, SLLM_K1_STREAM_BLOCKS, SLLM_K1_UNROLL, SLLM_K1_NT,
  *   SLLM_K2_NT, SLLM_K2_MAX_GRID, SLLM_K2_UNROLL, SLLM_NOALLOC_PLAN_BLOCKS
  *                         kernel launch shapes, read at every launch (for
- *                         measurements and tests; the defaults are tuned).
+ *                         measurements and tests; the defaults are tuned, some
+ *                         by the size of the image).
  */
 #ifndef SLLM_H
 #define SLLM_H

@@ -118,26 +118,39 @@ uint32_t env_u32(const char* name, uint32_t dflt) {
 
 }  // namespace
 
-GatherShape gather_shape() {
+// The link needs about 170 KB of reads in flight (57 GB/s x 3 us); what is
+// beyond that waits in queues, and delays the image's last tiles.
+//  * A launch that moves a whole image of 5 MB or more runs 104 workgroups (13
+//    for each XCD) of 4 KiB tiles, 426 KB in flight.  Against 512 of 16 KiB (8
+//    MB): 10.4 MB 193.1 / 198.9 us, 41.8 MB 741.9 / 748.6, 250 MB 4354 / 4369,
+//    2.1 GB the same; also with 12 threads copying host memory meanwhile (743.9
+//    / 751.9 us).  96 to 128 workgroups are within 0.2 %; 144 to 192, which do
+//    not spread evenly, lose 3 %.
+//  * A smaller image ends before the queues fill, and 512 of 16 KiB put all of
+//    it in flight at once: 3.5 MB 73.5 / 76.9 us, 1.0 MB 26.5 / 34, 0.24 MB
+//    11.8 / 17.
+//  * Launches that move part of an image (a streamed batch, run or chunk)
+//    overlap on the copy streams; 64 of 16 KiB each keep the reads in flight
+//    near what the link needs.
+GatherShape gather_shape(bool whole, uint64_t bytes) {
     // read at every launch (a few getenv calls) so one process can compare shapes
+    const bool narrow = whole && bytes >= 5000000;
     GatherShape s;
-    s.blocks = env_u32("SLLM_K1_BLOCKS", 512);
+    s.blocks = whole ? env_u32("SLLM_K1_BLOCKS", narrow ? 104 : 512) : env_u32("SLLM_K1_STREAM_BLOCKS", 64);
     if (s.blocks == 0) s.blocks = 1;
-    s.stream_blocks = env_u32("SLLM_K1_STREAM_BLOCKS", 64);
-    if (s.stream_blocks == 0) s.stream_blocks = 1;
-    s.unroll = env_u32("SLLM_K1_UNROLL", 4);
-    if (s.unroll != 1 && s.unroll != 2 && s.unroll != 4) s.unroll = 4;
+    const uint32_t dflt = narrow ? 1 : 4;
+    s.unroll = env_u32("SLLM_K1_UNROLL", dflt);
+    if (s.unroll != 1 && s.unroll != 2 && s.unroll != 4) s.unroll = dflt;
     s.nontemporal = env_u32("SLLM_K1_NT", 0) != 0;
     return s;
 }
 
 namespace {
 
-int32_t launch_tiles(GatherArgs a, uint64_t tpc, uint64_t n_chunks, const GatherShape& sh, uint32_t blocks,
-                     hipStream_t stream) {
+int32_t launch_tiles(GatherArgs a, uint64_t tpc, uint64_t n_chunks, const GatherShape& sh, hipStream_t stream) {
     a.tiles_per_chunk = (uint32_t)tpc;
     a.n_tiles = (uint32_t)(n_chunks * tpc);
-    const uint32_t grid = a.n_tiles < blocks ? a.n_tiles : blocks;
+    const uint32_t grid = a.n_tiles < sh.blocks ? a.n_tiles : sh.blocks;
     const dim3 gd(grid), bd(kThreads);
     switch (sh.unroll * 2 + (sh.nontemporal ? 1 : 0)) {
         case 2: k1_gather<1, false><<<gd, bd, 0, stream>>>(a); break;
@@ -174,7 +187,7 @@ int32_t launch_gather_batch(uint8_t* dst, const uint8_t* const* srcs, const uint
         }
         return SLLM_OK;
     }
-    const GatherShape sh = gather_shape();
+    const GatherShape sh = gather_shape(/*whole=*/false, 0);
     GatherArgs a{};
     a.dst = dst;
     a.chunk = chunk;
@@ -186,7 +199,7 @@ int32_t launch_gather_batch(uint8_t* dst, const uint8_t* const* srcs, const uint
     }
     const uint64_t tpc = ceil_div(chunk, (uint64_t)kThreads * kVec * sh.unroll);
     if (tpc * n >= (1ull << 31)) return fail(SLLM_E_INVAL, "gather batch: chunk size too large");
-    return launch_tiles(a, tpc, n, sh, sh.stream_blocks, stream);
+    return launch_tiles(a, tpc, n, sh, stream);
 }
 
 int32_t launch_gather(const GatherLaunch& g, hipStream_t stream) {
@@ -194,7 +207,8 @@ int32_t launch_gather(const GatherLaunch& g, hipStream_t stream) {
     if (!g.table && g.n_chunks != 1) return fail(SLLM_E_INVAL, "gather: a single slot serves one chunk");
     if (g.chunk == 0 || g.n_chunks > ceil_div(g.total, g.chunk) - g.first_chunk)
         return fail(SLLM_E_INVAL, "gather: chunks past the end of the image");
-    const GatherShape sh = gather_shape();
+    const bool whole = g.first_chunk == 0 && g.n_chunks == ceil_div(g.total, g.chunk);
+    const GatherShape sh = gather_shape(whole, g.total);
     GatherArgs a{};
     a.dst = g.dst;
     a.table = g.table;
@@ -213,8 +227,6 @@ int32_t launch_gather(const GatherLaunch& g, hipStream_t stream) {
     }
     const uint64_t tile = (uint64_t)kThreads * kVec * sh.unroll;
     const uint64_t tpc = ceil_div(g.chunk, tile);
-    const bool whole = g.first_chunk == 0 && g.n_chunks == ceil_div(g.total, g.chunk);
-    const uint32_t blocks = whole ? sh.blocks : sh.stream_blocks;
     // launch at most 2^31 tiles at a time
     const uint64_t max_chunks = tpc > (1ull << 31) ? 0 : (1ull << 31) / tpc;
     if (max_chunks == 0) return fail(SLLM_E_INVAL, "gather: chunk size %llu too large", (unsigned long long)g.chunk);
@@ -222,7 +234,7 @@ int32_t launch_gather(const GatherLaunch& g, hipStream_t stream) {
         const uint64_t nc = g.n_chunks - c0 < max_chunks ? g.n_chunks - c0 : max_chunks;
         a.table = g.table ? g.table + c0 : nullptr;
         a.first_chunk = g.first_chunk + c0;
-        SLLM_TRY(launch_tiles(a, tpc, nc, sh, blocks, stream));
+        SLLM_TRY(launch_tiles(a, tpc, nc, sh, stream));
     }
     return SLLM_OK;
 }
