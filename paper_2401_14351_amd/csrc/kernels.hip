@@ -120,12 +120,14 @@ uint32_t env_u32(const char* name, uint32_t dflt) {
 
 // The link needs about 170 KB of reads in flight (57 GB/s x 3 us); what is
 // beyond that waits in queues, and delays the image's last tiles.
-//  * A launch that moves a whole image of 5 MB or more runs 104 workgroups (13
+//  * A launch that moves a whole image of 5 MB to 1 GiB runs 104 workgroups (13
 //    for each XCD) of 4 KiB tiles, 426 KB in flight.  Against 512 of 16 KiB (8
 //    MB): 10.4 MB 193.1 / 198.9 us, 41.8 MB 741.9 / 748.6, 250 MB 4354 / 4369,
-//    2.1 GB the same; also with 12 threads copying host memory meanwhile (743.9
-//    / 751.9 us).  96 to 128 workgroups are within 0.2 %; 144 to 192, which do
-//    not spread evenly, lose 3 %.
+//    1.05 GB 18233 / 18243; also with 12 threads copying host memory meanwhile
+//    (41.8 MB 743.9 / 751.9 us).  96 to 128 workgroups are within 0.2 %; 144 to
+//    192, which do not spread evenly, lose 3 %.  In larger images the last tiles
+//    no longer count and the deeper queue is as fast (2.1 GB) or faster (13.5 GB
+//    57.51 / 57.54 GB/s).
 //  * A smaller image ends before the queues fill, and 512 of 16 KiB put all of
 //    it in flight at once: 3.5 MB 73.5 / 76.9 us, 1.0 MB 26.5 / 34, 0.24 MB
 //    11.8 / 17.
@@ -134,7 +136,7 @@ uint32_t env_u32(const char* name, uint32_t dflt) {
 //    near what the link needs.
 GatherShape gather_shape(bool whole, uint64_t bytes) {
     // read at every launch (a few getenv calls) so one process can compare shapes
-    const bool narrow = whole && bytes >= 5000000;
+    const bool narrow = whole && bytes >= 5000000 && bytes < (1ull << 30);
     GatherShape s;
     s.blocks = whole ? env_u32("SLLM_K1_BLOCKS", narrow ? 104 : 512) : env_u32("SLLM_K1_STREAM_BLOCKS", 64);
     if (s.blocks == 0) s.blocks = 1;
