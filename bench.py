@@ -668,8 +668,8 @@ def k2_tile_paths(file_off, dev_off, sizes, T2):
     """How K2's tiles split between its paths for a whole-image repack: a tile
     whose plan block lies inside one tensor's data copies straight (source
     and destination agree mod 16) or through the byte funnel (they do not);
-    every other tile (tensor edges, padding, small tensors) takes the staged
-    general path."""
+    every other tile (tensor edges, padding, small tensors) goes wave by wave
+    from the tensor its plan block names."""
     import numpy as np
 
     o = np.asarray(file_off, dtype=np.int64)
