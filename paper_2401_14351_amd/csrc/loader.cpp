@@ -236,6 +236,17 @@ int32_t mark_end(const sllm_ckpt* h, hipStream_t s) {
     return SLLM_OK;
 }
 
+// Whether `s` is capturing (the query fails only on the null stream, which
+// cannot capture, while another stream does).  Captured work is given no end
+// event: it would end with no replay, and HIP refuses to query an event of a
+// capture, which leaves an error pending for the next launch check.
+bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // leave no error behind for later launch checks
+    return false;
+}
+
 // Make the copy streams wait for work already queued on `user`.
 int32_t fork_streams(sllm_ckpt* h, hipStream_t user) {
     SLLM_HIP(hipEventRecord(h->fork_ev, user));
@@ -750,6 +761,7 @@ extern "C" int32_t sllm_load(sllm_ckpt* h, void* dev_dst, uint64_t dst_bytes, vo
     if (!guard.ok()) return fail(SLLM_E_HIP, "cannot make device %d current", h->device);
     SLLM_TRY(check_device_range(dev_dst, h->dev_total, h->device, "destination"));
     hipStream_t user = static_cast<hipStream_t>(stream);
+    const bool capturing = is_capturing(user);
     const double t0 = now_s();
     h->stats.bytes_loaded = 0;
     h->stats.bytes_read = 0;
@@ -778,7 +790,7 @@ extern "C" int32_t sllm_load(sllm_ckpt* h, void* dev_dst, uint64_t dst_bytes, vo
         (void)hipStreamSynchronize(user);
         return st;
     }
-    if (h->dev_total) {
+    if (h->dev_total && !capturing) {
         st = mark_end(h, user);
         if (st != SLLM_OK) {
             (void)hipStreamSynchronize(user);
@@ -819,20 +831,12 @@ extern "C" int32_t sllm_repack(const sllm_ckpt* h, const void* src_dev, uint64_t
     const uint8_t* src = static_cast<const uint8_t*>(src_dev);
     // The end event rides on the kernel: a recorded event is a packet of its own
     // with a system-scope fence, 2.6 us on the stream after each repack (40 MB
-    // in and out: 10.4 -> 7.8 us a repack).  Under capture it is recorded.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool eager = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-    int32_t st;
-    if (eager) {
-        hipEvent_t end = nullptr;
-        SLLM_TRY(free_end_event(h, &end));
-        st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s, end);
-        if (st == SLLM_OK) use_end_event(h);
-    } else {
-        (void)hipGetLastError();
-        st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s);
-        if (st == SLLM_OK) st = mark_end(h, s);
-    }
+    // in and out: 10.4 -> 7.8 us a repack).
+    const bool capturing = is_capturing(s);
+    hipEvent_t end = nullptr;
+    if (!capturing) SLLM_TRY(free_end_event(h, &end));
+    const int32_t st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s, end);
+    if (st == SLLM_OK && !capturing) use_end_event(h);
     if (st != SLLM_OK) (void)hipStreamSynchronize(s);  // close could not wait for what was launched
     return st;
 } SLLM_CATCH_ALL

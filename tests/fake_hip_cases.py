@@ -1,0 +1,86 @@
+"""Cases of test_host_hip.py, each run in a process of its own (usage:
+fake_hip_cases.py FAKE_LIBRARY CASE DIRECTORY): the library's host code over
+the HIP runtime of tests/native/fake_hip.cpp, which stands in for the real one
+and must be loaded first.  Nothing here may import torch, which brings the real
+runtime with it."""
+
+import ctypes as C
+import os
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+sys.modules["torch"] = None  # "import torch" raises ImportError
+
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_records_captured", "fake_bad_calls"):
+    getattr(fake, _name).restype = C.c_uint64
+fake.fake_bad_list.restype = C.c_char_p
+fake.fake_limit.argtypes = [C.c_uint64]
+fake.fake_fail_launch.argtypes = [C.c_int64]
+fake.fake_stream.restype = C.c_void_p
+fake.fake_capture.argtypes = [C.c_void_p, C.c_int]
+fake.fake_device_alloc.restype = C.c_void_p
+fake.fake_device_alloc.argtypes = [C.c_uint64]
+
+import numpy as np  # noqa: E402
+
+from paper_2401_14351_amd import binding  # noqa: E402
+
+KiB, MiB = 1 << 10, 1 << 20
+NO_LIMIT = (1 << 64) - 1
+
+
+def convert(d, sizes, A=16, chunk=64 * KiB):
+    d = os.path.join(sys.argv[3], d)
+    binding.convert(((f"t{i}", "i8", (n,), np.full(n, i % 251, np.uint8)) for i, n in enumerate(sizes)), d, A, chunk)
+    return d
+
+
+def total(sizes, A):
+    return sum(-(-n // A) * A for n in sizes)
+
+
+class Buffers:
+    """Device buffers for a repack of `sizes` from A into A2."""
+
+    def __init__(self, sizes, A, A2):
+        self.n, self.n2 = total(sizes, A), total(sizes, A2)
+        self.src, self.dst = fake.fake_device_alloc(self.n), fake.fake_device_alloc(self.n2)
+
+    def repack(self, ck, stream):
+        return binding.lib().sllm_repack(ck._h, self.src, self.n, self.dst, self.n2, stream)
+
+
+SIZES = [1000, 0, 70_000, 5, 333_333]
+
+
+def case_events_under_capture():
+    """Captured loads and repacks record no event, and no event of a capture is
+    queried or waited for: neither by calls of the same capture, nor by eager
+    ones on another stream meanwhile, nor at close."""
+    d = convert("c", SIZES)
+    b = Buffers(SIZES, 16, 256)
+    s, other = fake.fake_stream(), fake.fake_stream()
+    pool = binding.Pool(64 * KiB, 32)
+    pool.cache(d)
+    ck = binding.Checkpoint(d, pool=pool, dev_alignment=256)
+    assert b.repack(ck, s) == 0
+    fake.fake_capture(s, 1)
+    for _ in range(3):
+        assert b.repack(ck, s) == 0
+        ck.load(b.dst, b.n2, s)
+        assert b.repack(ck, other) == 0  # eager
+    fake.fake_capture(s, 0)
+    for _ in range(6):  # more than the events a call looks at
+        assert b.repack(ck, s) == 0
+        ck.load(b.dst, b.n2, other)
+    ck.close()
+    assert fake.fake_records_captured() == 0
+    assert fake.fake_bad_calls() == 0, fake.fake_bad_list()
+    assert fake.fake_pending() == 0
+
+
+if __name__ == "__main__":
+    globals()["case_" + sys.argv[2]]()
+    print("ok")

@@ -1,0 +1,238 @@
+// A HIP runtime for host tests without a GPU: memory is host memory, copies
+// are memcpy, kernels are logged and not run, and events complete at once.
+// Loaded before libsllm.so with global symbols, it takes the place of the real
+// runtime for that library.  It keeps what the tests assert on: which blocks
+// were allocated and freed, what was called on a capturing stream or on an
+// event of a capture, and the error that stays pending until hipGetLastError.
+// Calls can be told to fail.
+#define __HIP_PLATFORM_AMD__
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+
+struct ihipStream_t {
+    bool capturing = false;
+};
+struct ihipEvent_t {
+    bool captured = false;  // recorded in a stream that was capturing
+};
+
+namespace {
+
+std::map<uintptr_t, size_t> device_mem;
+uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls;
+uint64_t device_limit = UINT64_MAX, device_used;
+int64_t fail_launch = -1;  // the launch after this many more fails
+std::string bad_calls;     // what was called on a capturing stream or a captured event
+hipError_t pending = hipSuccess;
+std::map<const void*, std::string> kernels;
+struct {
+    dim3 grid, block;
+    size_t shmem;
+    hipStream_t stream;
+} call;
+
+hipError_t err(hipError_t e) {
+    if (e != hipSuccess) pending = e;
+    return e;
+}
+
+bool capturing(hipStream_t s) { return s && s->capturing; }
+
+hipError_t bad(const char* what, hipError_t e) {
+    ++n_bad_calls;
+    bad_calls += std::string(what) + ";";
+    return err(e);
+}
+
+hipError_t launched(const void*, void**) {
+    ++n_launch;
+    if (fail_launch == 0) {
+        fail_launch = -1;
+        return err(hipErrorLaunchFailure);
+    }
+    if (fail_launch > 0) --fail_launch;
+    return hipSuccess;
+}
+
+}  // namespace
+
+extern "C" {
+
+// ---- the tests' side --------------------------------------------------------
+uint64_t fake_mallocs() { return n_malloc; }
+uint64_t fake_frees() { return n_free; }
+uint64_t fake_launches() { return n_launch; }
+uint64_t fake_used() { return device_used; }
+uint64_t fake_records_captured() { return n_record_captured; }
+uint64_t fake_bad_calls() { return n_bad_calls; }
+const char* fake_bad_list() { return bad_calls.c_str(); }
+int fake_pending() { return (int)pending; }
+void fake_limit(uint64_t bytes) { device_limit = bytes; }
+void fake_fail_launch(int64_t after) { fail_launch = after; }
+void* fake_stream() { return new ihipStream_t; }
+void fake_capture(void* s, int on) { static_cast<ihipStream_t*>(s)->capturing = on != 0; }
+void* fake_device_alloc(uint64_t n) {
+    void* p = nullptr;
+    return hipMalloc(&p, n) == hipSuccess ? p : nullptr;
+}
+
+// ---- memory -------------------------------------------------------------------
+hipError_t hipMalloc(void** p, size_t n) {
+    *p = nullptr;
+    if (n > device_limit || device_used > device_limit - n) return err(hipErrorOutOfMemory);
+    *p = std::aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+    device_mem[(uintptr_t)*p] = n;
+    device_used += n;
+    ++n_malloc;
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+    auto it = device_mem.find((uintptr_t)p);
+    if (it == device_mem.end()) return p ? err(hipErrorInvalidValue) : hipSuccess;
+    device_used -= it->second;
+    device_mem.erase(it);
+    std::free(p);
+    ++n_free;
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    *p = std::aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
+    *d = h;
+    return hipSuccess;
+}
+static std::map<uintptr_t, size_t>::iterator holder(const void* p) {
+    auto it = device_mem.upper_bound((uintptr_t)p);
+    if (it == device_mem.begin()) return device_mem.end();
+    --it;
+    return (uintptr_t)p < it->first + it->second ? it : device_mem.end();
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+    if (holder(p) == device_mem.end()) return err(hipErrorInvalidValue);
+    std::memset(a, 0, sizeof *a);
+    a->type = hipMemoryTypeDevice;
+    return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* n, hipDeviceptr_t p) {
+    auto it = holder(p);
+    if (it == device_mem.end()) return err(hipErrorInvalidValue);
+    *base = (void*)it->first;
+    *n = it->second;
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    if (!capturing(st)) std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+    static void* scratch = std::aligned_alloc(4096, 16 << 20);
+    *p = scratch;
+    return hipSuccess;
+}
+
+// ---- device, errors -----------------------------------------------------------
+hipError_t hipGetDeviceCount(int* n) {
+    *n = 1;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = pending;
+    pending = hipSuccess;
+    return e;
+}
+const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "an error"; }
+
+// ---- streams, events ----------------------------------------------------------
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+    *s = new ihipStream_t;
+    return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) {
+    delete s;
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    return capturing(s) ? bad("hipStreamSynchronize", hipErrorStreamCaptureUnsupported) : hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+    *st = capturing(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    if (e->captured && s) s->capturing = true;  // the stream joins the capture
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+    *e = new ihipEvent_t;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) {
+    delete e;
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    e->captured = capturing(s);
+    if (e->captured) ++n_record_captured;
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) {
+    return e->captured ? bad("hipEventQuery", hipErrorCapturedEvent) : hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    return e->captured ? bad("hipEventSynchronize", hipErrorCapturedEvent) : hipSuccess;
+}
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+    *ms = 0;
+    return hipSuccess;
+}
+
+// ---- launches -----------------------------------------------------------------
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shmem, hipStream_t s) {
+    call = {grid, block, shmem, s};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hipStream_t* s) {
+    *grid = call.grid;
+    *block = call.block;
+    *shmem = call.shmem;
+    *s = call.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) { return launched(f, args); }
+hipError_t hipExtLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s, hipEvent_t, hipEvent_t end,
+                              int) {
+    if (end && capturing(s)) return bad("hipExtLaunchKernel with an event", hipErrorStreamCaptureUnsupported);
+    if (end) end->captured = false;
+    return launched(f, args);
+}
+void** __hipRegisterFatBinary(const void*) {
+    static void* h;
+    return &h;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* f, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+    kernels[f] = name;
+}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+}

@@ -1,0 +1,38 @@
+"""The library's host code on the CPU, over a stand-in HIP runtime
+(tests/native/fake_hip.cpp): what it calls under capture, what it keeps and
+frees, and what it does when calls fail.  Each case of fake_hip_cases.py runs
+in a process of its own."""
+
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from paper_2401_14351_amd import binding
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+pytestmark = [pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available"),
+              pytest.mark.skipif(not os.path.exists(binding.LIB_PATH), reason="libsllm.so not built")]
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-shared", "-fPIC", f"-I{ROCM}/include",
+                    os.path.join(HERE, "native", "fake_hip.cpp"), "-o", so], check=True)
+    return so
+
+
+def run(fake, tmp_path, case):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "fake_hip_cases.py"), fake, case, str(tmp_path)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("case", ["events_under_capture"])
+def test_host_code(fake, tmp_path, case):
+    run(fake, tmp_path, case)
