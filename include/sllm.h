@@ -43,6 +43,10 @@
  *     back to the library at close and stay idle for the next handle (at most
  *     64 MiB in 32 blocks per device; more is freed, and the idle ones are
  *     freed when an allocation of theirs finds no memory).
+ *   - A load or repack may be captured into a HIP graph; the handle must stay
+ *     open while the graph is replayed.  The device tables and staging of a
+ *     handle used that way are freed at close, which waits for the device and
+ *     so for replays under way.
  *   - Reader threads outlive the loads that start them: a finished reader
  *     waits idle (at most 64 per process, until the process ends) for the
  *     next load or pool fill, which then wakes it instead of starting a

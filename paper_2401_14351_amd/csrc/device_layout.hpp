@@ -73,8 +73,9 @@ constexpr int64_t kMixedEnd = INT64_MIN / 2;
 // The tables are complete on return.  The current device must be `device`.
 int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev_off, uint64_t dev_total,
                             uint64_t dev_align, uint64_t staging_chunks, uint64_t chunk, DeviceLayout* out);
-// No work may use the layout any more; its device must be current.
-void device_layout_free(DeviceLayout* l);
+// Give the layout's blocks back (park: no work may use them any more) or free
+// them, which waits for the device.  Its device must be current.
+void device_layout_free(DeviceLayout* l, bool park);
 
 // Move partition window [x0, x1), held contiguously at `src` (device memory,
 // or a device-visible mapping of pinned host memory), into the device image.

@@ -935,9 +935,11 @@ int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev
     return SLLM_OK;
 }
 
-void device_layout_free(DeviceLayout* l) {
-    block_give(&l->tables);
-    block_give(&l->stage);
+void device_layout_free(DeviceLayout* l, bool park) {
+    for (DeviceBlock* b : {&l->tables, &l->stage}) {
+        if (park) block_give(b);
+        else if (b->p) (void)hipFree(b->p);
+    }
     *l = DeviceLayout{};
 }
 

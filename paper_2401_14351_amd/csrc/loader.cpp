@@ -71,6 +71,7 @@ struct sllm_ckpt {
     mutable size_t end_look = 0;    // the next of end_evs to look at
     bool timed = false;             // t0/t1 bracket the last load
     DeviceLayout layout;            // device tables for A2 layouts
+    mutable bool captured = false;  // a graph may hold work of this handle, and no event ends its replays
     bool keep = false;              // SLLM_OPEN_CACHE: chunk k streams into slot k, kept afterwards
     const uint8_t** keep_table = nullptr;  // device table of the kept slots, until the pool adopts it
     std::atomic<bool> busy{false};
@@ -123,7 +124,9 @@ void release(sllm_ckpt* h) {
         }
         for (hipEvent_t e : {h->t0_ev, h->t1_ev})
             if (e) (void)hipEventDestroy(e);
-        device_layout_free(&h->layout);
+        // a replay may still run: hipFree waits for the device, where the next
+        // handle would rewrite a parked block under it
+        device_layout_free(&h->layout, /*park=*/!h->captured);
     }
     if (h->keep_table) pool_free_table(h->pool, h->keep_table);
     if (h->pool) {
@@ -762,6 +765,7 @@ extern "C" int32_t sllm_load(sllm_ckpt* h, void* dev_dst, uint64_t dst_bytes, vo
     SLLM_TRY(check_device_range(dev_dst, h->dev_total, h->device, "destination"));
     hipStream_t user = static_cast<hipStream_t>(stream);
     const bool capturing = is_capturing(user);
+    if (capturing) h->captured = true;
     const double t0 = now_s();
     h->stats.bytes_loaded = 0;
     h->stats.bytes_read = 0;
@@ -833,6 +837,7 @@ extern "C" int32_t sllm_repack(const sllm_ckpt* h, const void* src_dev, uint64_t
     // with a system-scope fence, 2.6 us on the stream after each repack (40 MB
     // in and out: 10.4 -> 7.8 us a repack).
     const bool capturing = is_capturing(s);
+    if (capturing) h->captured = true;
     hipEvent_t end = nullptr;
     if (!capturing) SLLM_TRY(free_end_event(h, &end));
     const int32_t st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s, end);

@@ -81,6 +81,48 @@ def case_events_under_capture():
     assert fake.fake_pending() == 0
 
 
+def case_close_after_capture():
+    """The device tables and staging of a handle whose loads or repacks were
+    captured are freed at close (hipFree waits for the device, so for replays
+    too); those of other handles stay for the next one."""
+    d = convert("c", SIZES)
+    b = Buffers(SIZES, 16, 256)
+    s = fake.fake_stream()
+    pool = binding.Pool(64 * KiB, 32)
+    pool.cache(d)
+
+    def frees(engine, work):
+        """Blocks the close of a handle frees."""
+        ck = binding.Checkpoint(d, pool=pool, dev_alignment=256, engine=engine)
+        work(ck)
+        before = fake.fake_frees()
+        ck.close()
+        return fake.fake_frees() - before
+
+    def captured(f):
+        def run(ck):
+            f(ck)  # also eagerly
+            fake.fake_capture(s, 1)
+            f(ck)
+            fake.fake_capture(s, 0)
+            f(ck)
+        return run
+
+    def repack(ck):
+        assert b.repack(ck, s) == 0
+
+    def load(ck):
+        ck.load(b.dst, b.n2, s)
+
+    for engine, blocks in (("kernel", 1), ("sdma", 2)):
+        for work in (repack, load):
+            if engine == "sdma" and work is load:
+                continue  # its copy streams would have to leave the capture again
+            assert frees(engine, work) == 0, (engine, work)
+            assert frees(engine, captured(work)) == blocks, (engine, work)
+            assert frees(engine, work) == 0, (engine, work)
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]]()
     print("ok")

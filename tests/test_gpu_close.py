@@ -153,3 +153,46 @@ def test_repack_captured_in_a_graph(torch_cuda, tmp_path):
             assert out.cpu().numpy().tobytes() == want, f"replay {k}"
             assert other.cpu().numpy().tobytes() == want, f"eager {k}"
         del g
+
+
+@pytest.mark.parametrize("what", ["repack", "load"])
+def test_close_waits_for_replays(torch_cuda, tmp_path, what):
+    """A captured repack, or cached load into a device layout, replayed on a
+    non-blocking stream: close waits for the replays, which no event of the
+    handle ends, so the next handle's tables cannot take the place of those
+    they read."""
+    torch = torch_cuda
+    d, tensors = write(tmp_path, "graph", 46, A=1)
+    index = oracle.make_index(tensors, 1, C)
+    image = bytes(oracle.partition_bytes(tensors, 1)[:index.total_bytes])
+    want = bytes(oracle.repack(image, index, 256))
+    src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+    out = torch.empty(len(want), dtype=torch.uint8, device="cuda:0")
+    n = -(-index.total_bytes // C)
+    with binding.Pool(C, n) as pool:
+        pool.cache(d)
+        ck = binding.Checkpoint(d, pool=pool, dev_alignment=256)
+
+        def work(stream):
+            ck.repack(src, out, stream) if what == "repack" else ck.load_into(out, stream)
+
+        side = torch.cuda.Stream()
+        work(side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            work(torch.cuda.current_stream())
+        out.fill_(0xA5)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(8 if what == "repack" else 2):
+                g.replay()
+        assert not side.query(), "the replays ended too soon to show anything"
+        ck.close()
+        idle = side.query()
+        with binding.Checkpoint(d, pool=pool, dev_alignment=4096):  # other tables of the same size
+            torch.cuda.synchronize()
+        assert idle, "close returned while a replay still ran"
+        assert out.cpu().numpy().tobytes() == want
+        del g
+        pool.evict(d)
