@@ -789,9 +789,12 @@ extern "C" int32_t sllm_load(sllm_ckpt* h, void* dev_dst, uint64_t dst_bytes, vo
         // a load that failed part way may have queued copies or launches
         // before the failing call: let them finish, so that the caller may
         // free the destination as soon as the error is returned (the copy
-        // streams are the handle's own, invisible to the caller's allocator)
-        for (hipStream_t s : h->streams) (void)hipStreamSynchronize(s);
-        (void)hipStreamSynchronize(user);
+        // streams are the handle's own, invisible to the caller's allocator).
+        // Under capture nothing runs yet, and HIP refuses to wait.
+        if (!capturing) {
+            for (hipStream_t s : h->streams) (void)hipStreamSynchronize(s);
+            (void)hipStreamSynchronize(user);
+        }
         return st;
     }
     if (h->dev_total && !capturing) {
@@ -842,7 +845,8 @@ extern "C" int32_t sllm_repack(const sllm_ckpt* h, const void* src_dev, uint64_t
     if (!capturing) SLLM_TRY(free_end_event(h, &end));
     const int32_t st = launch_scatter_window(h->layout, dst, src, 0, h->ix.total, /*src_is_host=*/false, s, end);
     if (st == SLLM_OK && !capturing) use_end_event(h);
-    if (st != SLLM_OK) (void)hipStreamSynchronize(s);  // close could not wait for what was launched
+    // close could not wait for what was launched (under capture nothing was)
+    if (st != SLLM_OK && !capturing) (void)hipStreamSynchronize(s);
     return st;
 } SLLM_CATCH_ALL
 

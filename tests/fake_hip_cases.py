@@ -13,7 +13,8 @@ sys.path.insert(0, ROOT)
 sys.modules["torch"] = None  # "import torch" raises ImportError
 
 fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
-for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_records_captured", "fake_bad_calls"):
+for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_records_captured", "fake_bad_calls",
+              "fake_waits"):
     getattr(fake, _name).restype = C.c_uint64
 fake.fake_bad_list.restype = C.c_char_p
 fake.fake_limit.argtypes = [C.c_uint64]
@@ -121,6 +122,27 @@ def case_close_after_capture():
             assert frees(engine, work) == 0, (engine, work)
             assert frees(engine, captured(work)) == blocks, (engine, work)
             assert frees(engine, work) == 0, (engine, work)
+
+
+def case_failure_under_capture():
+    """A repack or load that fails under capture returns its error and makes no
+    call that HIP refuses on a capturing stream; eagerly it waits for the stream."""
+    d = convert("c", SIZES)
+    b = Buffers(SIZES, 16, 256)
+    s = fake.fake_stream()
+    pool = binding.Pool(64 * KiB, 32)
+    pool.cache(d)
+    with binding.Checkpoint(d, pool=pool, dev_alignment=256) as ck:
+        for capture in (1, 0):
+            for work in (lambda: b.repack(ck, s), lambda: binding.lib().sllm_load(ck._h, b.dst, b.n2, s)):
+                fake.fake_capture(s, capture)
+                fake.fake_fail_launch(0)
+                waits = fake.fake_waits()
+                assert work() == -5
+                fake.fake_capture(s, 0)
+                assert (fake.fake_waits() > waits) == (not capture)
+    assert fake.fake_bad_calls() == 0, fake.fake_bad_list()
+    assert fake.fake_pending() == 0
 
 
 if __name__ == "__main__":

@@ -24,7 +24,7 @@ struct ihipEvent_t {
 namespace {
 
 std::map<uintptr_t, size_t> device_mem;
-uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls;
+uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls, n_wait;
 uint64_t device_limit = UINT64_MAX, device_used;
 int64_t fail_launch = -1;  // the launch after this many more fails
 std::string bad_calls;     // what was called on a capturing stream or a captured event
@@ -69,6 +69,7 @@ uint64_t fake_frees() { return n_free; }
 uint64_t fake_launches() { return n_launch; }
 uint64_t fake_used() { return device_used; }
 uint64_t fake_records_captured() { return n_record_captured; }
+uint64_t fake_waits() { return n_wait; }
 uint64_t fake_bad_calls() { return n_bad_calls; }
 const char* fake_bad_list() { return bad_calls.c_str(); }
 int fake_pending() { return (int)pending; }
@@ -172,6 +173,7 @@ hipError_t hipStreamDestroy(hipStream_t s) {
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
+    ++n_wait;
     return capturing(s) ? bad("hipStreamSynchronize", hipErrorStreamCaptureUnsupported) : hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
