@@ -60,20 +60,19 @@ extern "C" int32_t sllm_export_create(const void* dev_ptr, uint64_t bytes, int32
         if (e != hipSuccess) {
             (void)hipEventDestroy(ex->ev);
             delete ex;
-            return fail(SLLM_E_HIP, "%s: %s", what, hipGetErrorString(e));
+            return fail(SLLM_E_HIP, "%s: %s", what, hip_message(e));
         }
         std::memcpy(desc->event_handle, &eh, sizeof eh);
         desc->flags |= SLLM_IPC_HAS_EVENT;
     } else {
         // no interprocess events here: finish the load before handing out the buffer
-        log_msg(1, "%s failed (%s); the export synchronizes on the host instead", what, hipGetErrorString(e));
+        log_msg(1, "%s failed (%s); the export synchronizes on the host instead", what, hip_message(e));
         if (ex->ev) (void)hipEventDestroy(ex->ev);
         ex->ev = nullptr;
-        (void)hipGetLastError();
         e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             delete ex;
-            return fail(SLLM_E_HIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+            return fail(SLLM_E_HIP, "hipStreamSynchronize: %s", hip_message(e));
         }
     }
     std::memcpy(desc->mem_handle, &mh, sizeof mh);
@@ -138,7 +137,7 @@ extern "C" int32_t sllm_import_open(const sllm_ipc_desc* desc, void* stream, voi
         if (im->ev) (void)hipEventDestroy(im->ev);
         if (im->base) (void)hipIpcCloseMemHandle(im->base);
         delete im;
-        return fail(code, "%s: %s", what, hipGetErrorString(e));
+        return fail(code, "%s: %s", what, hip_message(e));
     }
     *dev_ptr = static_cast<uint8_t*>(im->base) + desc->offset;
     *out = im;
@@ -152,6 +151,6 @@ extern "C" int32_t sllm_import_close(sllm_import* im) try {
     if (im->ev) (void)hipEventDestroy(im->ev);
     hipError_t e = im->base ? hipIpcCloseMemHandle(im->base) : hipSuccess;
     delete im;
-    if (e != hipSuccess) return fail(SLLM_E_HIP, "hipIpcCloseMemHandle: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return fail(SLLM_E_HIP, "hipIpcCloseMemHandle: %s", hip_message(e));
     return SLLM_OK;
 } SLLM_CATCH_ALL

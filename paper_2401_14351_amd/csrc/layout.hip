@@ -875,7 +875,7 @@ int32_t block_take(int device, uint64_t bytes, DeviceBlock* out) {
         for (const DeviceBlock& b : idle) (void)hipFree(b.p);
         e = hipMalloc(&p, want);
     }
-    if (e != hipSuccess) return fail(SLLM_E_HIP, "hipMalloc(%llu bytes) failed: %s", (unsigned long long)want, hipGetErrorString(e));
+    if (e != hipSuccess) return fail(SLLM_E_HIP, "hipMalloc(%llu bytes) failed: %s", (unsigned long long)want, hip_message(e));
     out->p = static_cast<uint8_t*>(p);
     out->bytes = want;
     return SLLM_OK;
@@ -1023,7 +1023,7 @@ int32_t scratch_of(int device, uint8_t** out) {
         void* p = nullptr;
         const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !p)
-            return fail(SLLM_E_HIP, "hipGetSymbolAddress(scratch) on device %d failed: %s", device, hipGetErrorString(e));
+            return fail(SLLM_E_HIP, "hipGetSymbolAddress(scratch) on device %d failed: %s", device, hip_message(e));
         g_scratch[device] = static_cast<uint8_t*>(p);
     }
     *out = g_scratch[device];

@@ -194,7 +194,7 @@ int32_t ensure_streams(sllm_ckpt* h) {
             if (ev) (void)hipEventDestroy(ev);
         for (hipStream_t s : streams)
             if (s) (void)hipStreamDestroy(s);
-        return fail(SLLM_E_HIP, "creating %u copy streams: %s", h->n_streams, hipGetErrorString(e));
+        return fail(SLLM_E_HIP, "creating %u copy streams: %s", h->n_streams, hip_message(e));
     }
     h->streams = std::move(streams);
     h->join_ev = std::move(join_ev);
@@ -487,7 +487,7 @@ class GpuSink final : public BatchSink {
         hipEvent_t ev = h_->slots[token].done;
         const hipError_t e = block ? hipEventSynchronize(ev) : hipEventQuery(ev);
         if (e == hipErrorNotReady) return 0;
-        if (e != hipSuccess) return fail(SLLM_E_HIP, "waiting for a batch: %s", hipGetErrorString(e));
+        if (e != hipSuccess) return fail(SLLM_E_HIP, "waiting for a batch: %s", hip_message(e));
         return 1;
     }
 
@@ -704,7 +704,7 @@ extern "C" int32_t sllm_open(const char* dir, const sllm_open_opts* opts, sllm_c
     }
     auto hip_ok = [&](hipError_t e, const char* what) {
         if (e == hipSuccess) return true;
-        fail(SLLM_E_HIP, "%s failed: %s", what, hipGetErrorString(e));
+        fail(SLLM_E_HIP, "%s failed: %s", what, hip_message(e));
         return false;
     };
     if ((o.flags & SLLM_OPEN_TIMING) &&

@@ -126,7 +126,7 @@ int32_t pool_chunk_table(sllm_pool* p, const std::vector<uint32_t>& ids, const u
     if (he == hipSuccess) he = hipMemcpy(d, table.data(), table.size() * sizeof(void*), hipMemcpyHostToDevice);
     if (he != hipSuccess) {
         if (d) (void)hipFree(d);
-        return fail(SLLM_E_HIP, "chunk table upload failed: %s", hipGetErrorString(he));
+        return fail(SLLM_E_HIP, "chunk table upload failed: %s", hip_message(he));
     }
     *out = d;
     return SLLM_OK;
@@ -230,14 +230,14 @@ extern "C" int32_t sllm_pool_create(uint64_t chunk_size, uint64_t n_chunks, int3
         hipError_t e = hipHostMalloc(&h, k * stride, hipHostMallocDefault);
         if (e != hipSuccess) {
             destroy_pool(p);
-            return fail(SLLM_E_HIP, "hipHostMalloc(%llu bytes) failed: %s", (unsigned long long)(k * stride), hipGetErrorString(e));
+            return fail(SLLM_E_HIP, "hipHostMalloc(%llu bytes) failed: %s", (unsigned long long)(k * stride), hip_message(e));
         }
         p->arenas.push_back(h);
         void* d = nullptr;
         e = hipHostGetDevicePointer(&d, h, 0);
         if (e != hipSuccess) {
             destroy_pool(p);
-            return fail(SLLM_E_HIP, "hipHostGetDevicePointer failed: %s", hipGetErrorString(e));
+            return fail(SLLM_E_HIP, "hipHostGetDevicePointer failed: %s", hip_message(e));
         }
         for (uint64_t i = 0; i < k; ++i) {
             p->host.push_back(static_cast<uint8_t*>(h) + i * stride);

@@ -145,6 +145,44 @@ def case_failure_under_capture():
     assert fake.fake_pending() == 0
 
 
+def case_error_not_left_pending():
+    """An open whose device memory cannot be had, and a load, repack or pool
+    whose HIP call fails, leave no error for the next call's launch check."""
+    d = convert("c", SIZES)
+    b = Buffers(SIZES, 16, 256)
+    s = fake.fake_stream()
+    pool = binding.Pool(64 * KiB, 32)
+    pool.cache(d)
+    for room in (0, 300 * KiB):  # not for the tables; for the tables, not for the staging
+        fake.fake_limit(fake.fake_used() + room)
+        for _ in range(2):
+            try:
+                binding.Checkpoint(d, pool=pool, dev_alignment=256, engine="sdma", n_streams=4)
+            except binding.SllmError as e:
+                assert e.code == -5, e
+            else:
+                raise AssertionError("the open succeeded")
+            assert fake.fake_pending() == 0
+        if room:
+            with binding.Checkpoint(d, pool=pool, dev_alignment=256) as ck:  # the kernel engine stages nothing
+                ck.load(b.dst, b.n2, s)
+        fake.fake_limit(NO_LIMIT)
+    with binding.Checkpoint(d, pool=pool, dev_alignment=256) as ck:
+        for work in (lambda: b.repack(ck, s), lambda: binding.lib().sllm_load(ck._h, b.dst, b.n2, s)):
+            fake.fake_fail_launch(0)
+            assert work() == -5
+            assert work() == 0
+    pool.evict(d)
+    fake.fake_limit(fake.fake_used())
+    try:
+        pool.cache(d)  # its chunk table
+    except binding.SllmError as e:
+        assert e.code == -5, e
+    else:
+        raise AssertionError("the fill succeeded")
+    assert fake.fake_pending() == 0
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]]()
     print("ok")

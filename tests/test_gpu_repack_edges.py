@@ -128,3 +128,26 @@ def test_staging_pieces(tmp_path, C, source):
                     assert (got[len(want):] == SENTINEL).all(), "bytes past the image were written"
             if source != "streamed":
                 pool.evict(str(tmp_path))
+
+
+def test_open_after_a_failed_allocation(tmp_path):
+    """An open whose staging no device could hold fails and leaves no HIP error
+    behind: the next open and load of the thread, which need none, succeed."""
+    import torch
+
+    rng = np.random.default_rng(5)
+    tensors = [(f"t{i}", "i8", (n,), rng.integers(0, 256, n, dtype=np.uint8)) for i, n in enumerate([(20 << 20) + 5, 77, 3000])]
+    binding.convert(iter(tensors), str(tmp_path), 16, 4 << 20)
+    index = oracle.make_index(tensors, 16, 4 << 20)
+    want = np.frombuffer(bytes(oracle.repack(bytes(oracle.partition_bytes(tensors, 16)[:index.total_bytes]), index, 256)), np.uint8)
+    with binding.Pool(4 << 20, 6) as pool:
+        pool.cache(str(tmp_path))
+        with pytest.raises(binding.SllmError) as ei:  # 4 MiB a stream at least: 64 TiB
+            binding.Checkpoint(str(tmp_path), pool=pool, engine="sdma", dev_alignment=256, n_streams=1 << 24)
+        assert ei.value.code == -5 and "hipMalloc" in ei.value.message
+        dst = torch.full((len(want) + 64,), SENTINEL, dtype=torch.uint8, device="cuda:0")
+        with binding.Checkpoint(str(tmp_path), pool=pool, dev_alignment=256) as ck:
+            ck.load_into(dst, torch.cuda.current_stream())
+            torch.cuda.synchronize()
+        assert np.array_equal(dst.cpu().numpy()[:len(want)], want)
+        pool.evict(str(tmp_path))
