@@ -829,8 +829,10 @@ int32_t launch_tables(const std::vector<uint64_t>& s, uint64_t align, uint64_t d
     return SLLM_OK;
 }
 
+constexpr int kMaxDevices = 64;
+
 std::mutex g_blocks_mu;
-std::vector<DeviceBlock> g_idle_blocks;
+std::vector<DeviceBlock> g_idle_blocks;  // oldest first
 
 }  // namespace
 
@@ -844,6 +846,7 @@ int32_t block_take(int device, uint64_t bytes, DeviceBlock* out) {
     {
         // the smallest idle block that fits, unless it would waste most of itself
         std::lock_guard<std::mutex> g(g_blocks_mu);
+        g_idle_blocks.reserve(kMaxIdleBlocks * kMaxDevices);  // giving a block back cannot fail
         size_t best = g_idle_blocks.size();
         for (size_t i = 0; i < g_idle_blocks.size(); ++i) {
             const DeviceBlock& b = g_idle_blocks[i];
@@ -883,22 +886,34 @@ int32_t block_take(int device, uint64_t bytes, DeviceBlock* out) {
 
 void block_give(DeviceBlock* b) {
     if (!b->p) return;
-    bool kept = false;
-    {
+    DeviceBlock drop[kMaxIdleBlocks];
+    size_t n_drop = 0;
+    if (b->bytes > kMaxIdleBlockBytes) {
+        drop[n_drop++] = *b;
+    } else {
+        // the device's oldest idle blocks make room, so that sizes no handle
+        // takes any more do not fill the list for good
         std::lock_guard<std::mutex> g(g_blocks_mu);
-        uint64_t held = 0;
-        size_t count = 0;
+        uint64_t held = b->bytes;
+        size_t count = 1;
         for (const DeviceBlock& i : g_idle_blocks)
             if (i.device == b->device) {
                 held += i.bytes;
                 ++count;
             }
-        if (count < kMaxIdleBlocks && b->bytes <= kMaxIdleBlockBytes && held <= kMaxIdleBlockBytes - b->bytes) {
-            g_idle_blocks.push_back(*b);
-            kept = true;
+        for (size_t i = 0; count > kMaxIdleBlocks || held > kMaxIdleBlockBytes;) {
+            if (g_idle_blocks[i].device != b->device) {
+                ++i;
+                continue;
+            }
+            held -= g_idle_blocks[i].bytes;
+            --count;
+            drop[n_drop++] = g_idle_blocks[i];
+            g_idle_blocks.erase(g_idle_blocks.begin() + (long)i);
         }
+        g_idle_blocks.push_back(*b);  // within the capacity block_take reserved
     }
-    if (!kept) (void)hipFree(b->p);
+    for (size_t i = 0; i < n_drop; ++i) (void)hipFree(drop[i].p);
     *b = DeviceBlock{};
 }
 
@@ -1010,7 +1025,6 @@ namespace sllm {
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 uint8_t* g_scratch[kMaxDevices] = {};
 

@@ -183,6 +183,50 @@ def case_error_not_left_pending():
     assert fake.fake_pending() == 0
 
 
+def case_idle_blocks():
+    """Blocks of closed handles wait for the next one, at most 64 MiB in 32
+    blocks, the oldest given up first: sizes no handle takes any more do not
+    keep later ones out."""
+    small, large = convert("s", [100]), convert("l", [1] * 20_000)
+    pool = binding.Pool(64 * KiB, 64)
+    pool.cache(small)
+    pool.cache(large)
+
+    def reopened(**opts):
+        """Allocations of the second of two handles opened and closed in a row."""
+        for _ in range(2):
+            before = fake.fake_mallocs()
+            binding.Checkpoint(pool=pool, **opts).close()
+        return fake.fake_mallocs() - before
+
+    base = fake.fake_used()
+    handles = [binding.Checkpoint(small, pool=pool, dev_alignment=256) for _ in range(40)]
+    for ck in handles:
+        ck.close()
+    assert fake.fake_used() - base == 32 * 64 * KiB
+    # 20,000 tensors' tables do not fit a 64 KiB block, whose place they take
+    assert reopened(ckpt_dir=large, dev_alignment=16) == 0
+    assert reopened(ckpt_dir=small, dev_alignment=16) == 0
+    # staging of sizes that are not asked for again
+    big = convert("b", [20 * MiB], chunk=64 * KiB)
+    with binding.Pool(64 * KiB, 320) as p2:
+        p2.cache(big)
+        for n in (3, 1, 2):
+            binding.Checkpoint(big, pool=p2, dev_alignment=16, engine="sdma", n_streams=n, io_threads=1).close()
+            assert fake.fake_used() - base <= 64 * MiB
+    assert reopened(ckpt_dir=large, dev_alignment=16) == 0
+    # more than all idle blocks may hold: freed at once, without the others
+    with binding.Pool(64 * KiB, 320) as p2:
+        p2.cache(big)
+        held = fake.fake_used()
+        binding.Checkpoint(big, pool=p2, dev_alignment=16, engine="sdma", n_streams=100).close()
+        assert abs(fake.fake_used() - held) <= MiB  # the tables only
+    # no memory: the idle blocks are given up for an allocation that needs it
+    fake.fake_limit(fake.fake_used())
+    with binding.Checkpoint(convert("x", [1] * 60_000), pool=None, dev_alignment=16, ring_slots=1):
+        pass
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]]()
     print("ok")
