@@ -70,7 +70,8 @@ constexpr int64_t kMixedEnd = INT64_MIN / 2;
 // Compute the tables and K2's plan on the device for the layout of `ix` at
 // dev_align (host offsets dev_off, dev_total bytes; both arguments must outlive
 // the layout), with `staging_chunks` HBM chunks of `chunk` bytes when asked.
-// The tables are complete on return.  The current device must be `device`.
+// The tables are complete on return and were read back and compared with the
+// host's.  The current device must be `device`.
 int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev_off, uint64_t dev_total,
                             uint64_t dev_align, uint64_t staging_chunks, uint64_t chunk, DeviceLayout* out);
 // Give the layout's blocks back (park: no work may use them any more) or free

@@ -18,6 +18,7 @@ for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_
     getattr(fake, _name).restype = C.c_uint64
 fake.fake_bad_list.restype = C.c_char_p
 fake.fake_limit.argtypes = [C.c_uint64]
+fake.fake_corrupt.argtypes = [C.c_uint64]
 fake.fake_fail_launch.argtypes = [C.c_int64]
 fake.fake_stream.restype = C.c_void_p
 fake.fake_capture.argtypes = [C.c_void_p, C.c_int]
@@ -224,6 +225,26 @@ def case_idle_blocks():
     # no memory: the idle blocks are given up for an allocation that needs it
     fake.fake_limit(fake.fake_used())
     with binding.Checkpoint(convert("x", [1] * 60_000), pool=None, dev_alignment=16, ring_slots=1):
+        pass
+
+
+def case_tables_are_checked():
+    """A wrong entry in any of the device's tables fails the open: file offset,
+    device offset or size, of the first, a middle and the last tensor of each
+    batch, and the totals."""
+    sizes = [(i * 7919) % 60_000 for i in range(2500)]
+    d = convert("c", sizes)
+    n = len(sizes)
+    for what in [3 * i + k for i in (0, 1, 1023, 1983, 1984, 1985, n - 1) for k in (0, 1, 2)] + [3 * n, 3 * n + 1]:
+        fake.fake_corrupt(what)
+        try:
+            binding.Checkpoint(d, dev_alignment=256, ring_slots=1).close()
+        except binding.SllmError as e:
+            assert e.code == -5 and "disagree" in e.message, e
+        else:
+            raise AssertionError(f"entry {what} was not checked")
+    fake.fake_corrupt(NO_LIMIT)
+    with binding.Checkpoint(d, dev_alignment=256, ring_slots=1):
         pass
 
 

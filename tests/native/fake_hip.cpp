@@ -1,7 +1,8 @@
 // A HIP runtime for host tests without a GPU: memory is host memory, copies
 // are memcpy, kernels are logged and not run, and events complete at once.
 // Loaded before libsllm.so with global symbols, it takes the place of the real
-// runtime for that library.  It keeps what the tests assert on: which blocks
+// runtime for that library.  The index-table kernel alone is carried out, from
+// its arguments, since the host reads the tables back.  It keeps what the tests assert on: which blocks
 // were allocated and freed, what was called on a capturing stream or on an
 // event of a capture, and the error that stays pending until hipGetLastError.
 // Calls can be told to fail.
@@ -13,6 +14,10 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <vector>
+
+#include "device_layout.hpp"
+#include "tables.hpp"
 
 struct ihipStream_t {
     bool capturing = false;
@@ -26,6 +31,7 @@ namespace {
 std::map<uintptr_t, size_t> device_mem;
 uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls, n_wait;
 uint64_t device_limit = UINT64_MAX, device_used;
+uint64_t corrupt = UINT64_MAX;  // 3 i + {0, 1, 2}: the table kernel writes a wrong o, d or s of tensor i
 int64_t fail_launch = -1;  // the launch after this many more fails
 std::string bad_calls;     // what was called on a capturing stream or a captured event
 hipError_t pending = hipSuccess;
@@ -49,13 +55,35 @@ hipError_t bad(const char* what, hipError_t e) {
     return err(e);
 }
 
-hipError_t launched(const void*, void**) {
+// the index-table kernel's work, one tensor after another
+void run_tables(const sllm::TableArgs& a) {
+    uint64_t o = a.o0, d = a.d0;
+    for (uint32_t j = 0; j < a.m; ++j) {
+        const uint64_t s = sllm::table_size(a, j), i = a.i0 + j;
+        a.size[i] = s + (corrupt == 3 * i + 2);
+        a.off[i] = o + (corrupt == 3 * i);
+        a.dev[i] = d + (corrupt == 3 * i + 1);
+        const uint64_t d_end = d + ((s + a.align_d - 1) & ~(a.align_d - 1));
+        for (uint64_t p = (d + sllm::kPlanBytes - 1) / sllm::kPlanBytes; p * sllm::kPlanBytes < d_end; ++p)
+            if (p >= a.p0 && p - a.p0 < a.n_plan)
+                a.plan[p - a.p0] = (p + 1) * sllm::kPlanBytes <= d + s ? (int64_t)(o - d) : sllm::kMixedTile + (int64_t)i;
+        o += (s + a.align_o - 1) & ~(a.align_o - 1);
+        d = d_end;
+    }
+    if (a.last) {
+        a.off[a.i0 + a.m] = o + (corrupt == 3 * (a.i0 + a.m));
+        a.dev[a.i0 + a.m] = d + (corrupt == 3 * (a.i0 + a.m) + 1);
+    }
+}
+
+hipError_t launched(const void* f, void** args) {
     ++n_launch;
     if (fail_launch == 0) {
         fail_launch = -1;
         return err(hipErrorLaunchFailure);
     }
     if (fail_launch > 0) --fail_launch;
+    if (kernels[f].find("k3_tables") != std::string::npos) run_tables(*static_cast<const sllm::TableArgs*>(args[0]));
     return hipSuccess;
 }
 
@@ -75,6 +103,7 @@ const char* fake_bad_list() { return bad_calls.c_str(); }
 int fake_pending() { return (int)pending; }
 void fake_limit(uint64_t bytes) { device_limit = bytes; }
 void fake_fail_launch(int64_t after) { fail_launch = after; }
+void fake_corrupt(uint64_t what) { corrupt = what; }
 void* fake_stream() { return new ihipStream_t; }
 void fake_capture(void* s, int on) { static_cast<ihipStream_t*>(s)->capturing = on != 0; }
 void* fake_device_alloc(uint64_t n) {

@@ -13,6 +13,7 @@ import pytest
 from paper_2401_14351_amd import binding
 
 HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 pytestmark = [pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available"),
@@ -23,6 +24,7 @@ pytestmark = [pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not av
 def fake(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-shared", "-fPIC", f"-I{ROCM}/include",
+                    f"-I{os.path.join(ROOT, 'include')}", f"-I{os.path.join(os.path.dirname(binding.LIB_PATH), 'csrc')}",
                     os.path.join(HERE, "native", "fake_hip.cpp"), "-o", so], check=True)
     return so
 
@@ -34,6 +36,6 @@ def run(fake, tmp_path, case):
 
 
 @pytest.mark.parametrize("case", ["events_under_capture", "close_after_capture", "failure_under_capture",
-                                  "error_not_left_pending", "idle_blocks"])
+                                  "error_not_left_pending", "idle_blocks", "tables_are_checked"])
 def test_host_code(fake, tmp_path, case):
     run(fake, tmp_path, case)
