@@ -381,23 +381,27 @@ class Checkpoint:
         self.load(buf.data_ptr(), buf.numel(), stream)
 
     def load_with_views(self, buf, stream=None, after_load: Optional[Callable[[], None]] = None):
-        """Load into ``buf`` while this thread builds the tensor views
-        (``sllm_load`` runs on a helper thread; ctypes releases the GIL during
-        the call) when there are many tensors, else load then build them.  ``after_load`` runs on that thread once the load is
-        enqueued.  Returns ``{name: view}``; the data are ready once
-        ``stream`` has been synchronized."""
-        table = self._table()
-        if len(table) < _THREADED_VIEWS_MIN:  # a helper thread costs more than these views
+        """Load into ``buf`` and return ``{name: view}``; the data are ready once
+        ``stream`` has been synchronized.  With many tensors this thread builds
+        the views while ``sllm_load`` runs on a helper thread (ctypes releases
+        the GIL during the call), else after it.  ``after_load`` runs on the
+        loading thread once the load is enqueued."""
+        n = C.c_uint64()
+        check(lib().sllm_tensor_index(self._h, None, 0, C.byref(n)))
+        if n.value < _THREADED_VIEWS_MIN:  # a helper thread costs more than these views
             self.load_into(buf, stream)
             if after_load is not None:
                 after_load()
-            return self._views(buf, table)
+            return self._views(buf, self._table())
+        table = self._table()
         err: List[BaseException] = []
+        names_read = threading.Event()
 
         def run():
             try:
                 self.load_into(buf, stream)
                 if after_load is not None:
+                    names_read.wait()  # after_load may close the handle, which the table's names live in
                     after_load()
             except BaseException as e:  # re-raised on the calling thread
                 err.append(e)
@@ -406,9 +410,10 @@ class Checkpoint:
         th.start()
         view_err = None
         try:
-            out = self._views(buf, table)
+            out = self._views(buf, table, names_read.set)
         except BaseException as e:  # e.g. a buffer too small for the views
             view_err = e
+        names_read.set()
         th.join()
         if err:  # the load's own error says more (SLLM_E_RANGE for a short buffer)
             raise err[0]
@@ -416,16 +421,20 @@ class Checkpoint:
             raise view_err
         return out
 
-    def _views(self, buf, table):
+    def _views(self, buf, table, names_read: Optional[Callable[[], None]] = None):
         """views(buf, self.tensors()), built natively from the index table.
         A tensor subclass or a torch function mode sees the calls of the
-        Python form instead."""
+        Python form instead.  ``names_read`` is called once the table's names
+        are no longer needed."""
         import torch
 
         if type(buf) is not torch.Tensor or torch._C._len_torch_function_stack():
-            return views(buf, self.tensors())
+            tensors = self.tensors()
+            if names_read is not None:
+                names_read()
+            return views(buf, tensors)
         _check_buffer(buf)
-        return _views_ext().build(buf, C.addressof(table), len(table))
+        return _views_ext().build(buf, C.addressof(table), len(table), names_read)
 
     def repack(self, src, dst, stream=None) -> None:
         _check_buffer(src)

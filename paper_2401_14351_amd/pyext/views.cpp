@@ -17,6 +17,8 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstring>
+#include <string>
 #include <vector>
 
 #include "sllm.h"
@@ -44,11 +46,13 @@ at::Tensor view_of(const at::Tensor& buf, at::Tensor* typed, const sllm_tensor_i
                           base.storage_offset() + off / isz);
 }
 
-// build(buf, table address, n) -> dict
+// build(buf, table address, n, names_read) -> dict.  The table's names belong to
+// the handle: they are copied first, and names_read (a callable or None) is
+// called when that is done, after which the handle may be closed.
 PyObject* build(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
-    if (nargs != 3 || !THPVariable_Check(args[0])) {
-        PyErr_SetString(PyExc_TypeError, "build(buf, table, n)");
+    if (nargs != 4 || !THPVariable_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError, "build(buf, table, n, names_read)");
         return nullptr;
     }
     const at::Tensor buf = THPVariable_Unpack(args[0]);
@@ -56,17 +60,27 @@ PyObject* build(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const uint64_t n = PyLong_AsUnsignedLongLong(args[2]);
     if (PyErr_Occurred()) return nullptr;
 
+    std::string names;  // each with its NUL
     at::Tensor typed[4];
     std::vector<at::Tensor> views;
     views.reserve(n);
+    bool failed = false;
     {
         pybind11::gil_scoped_release no_gil;
-        for (uint64_t i = 0; i < n; ++i) views.push_back(view_of(buf, typed, table[i]));
+        for (uint64_t i = 0; i < n; ++i) names.append(table[i].name, std::strlen(table[i].name) + 1);
+        if (args[3] != Py_None) {
+            pybind11::gil_scoped_acquire gil;
+            auto r = pybind11::reinterpret_steal<pybind11::object>(PyObject_CallNoArgs(args[3]));
+            failed = !r;
+        }
+        for (uint64_t i = 0; i < n && !failed; ++i) views.push_back(view_of(buf, typed, table[i]));
     }
+    if (failed) return nullptr;
     pybind11::object out = pybind11::reinterpret_steal<pybind11::object>(PyDict_New());
     if (!out) return nullptr;
-    for (uint64_t i = 0; i < n; ++i) {
-        auto name = pybind11::reinterpret_steal<pybind11::object>(PyUnicode_FromString(table[i].name));
+    const char* at = names.c_str();
+    for (uint64_t i = 0; i < n; ++i, at += std::strlen(at) + 1) {
+        auto name = pybind11::reinterpret_steal<pybind11::object>(PyUnicode_FromString(at));
         if (!name) return nullptr;
         auto v = pybind11::reinterpret_steal<pybind11::object>(THPVariable_Wrap(std::move(views[i])));
         if (!v || PyDict_SetItem(out.ptr(), name.ptr(), v.ptr()) != 0) return nullptr;
@@ -76,7 +90,7 @@ PyObject* build(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 }
 
 PyMethodDef kMethods[] = {{"build", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(build)), METH_FASTCALL,
-                           "build(buf, table, n) -> {name: view}"},
+                           "build(buf, table, n, names_read) -> {name: view}"},
                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_views", "Views over a loaded buffer.", -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 

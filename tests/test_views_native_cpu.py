@@ -74,3 +74,39 @@ def test_function_modes_see_the_calls(L, tmp_path):
         with Mode():
             ck._views(buf, ck._table())
         assert torch.Tensor.as_strided in calls
+
+
+@pytest.mark.parametrize("n", [10, 3000])
+@pytest.mark.parametrize("native", [True, False])
+def test_handle_closed_after_the_load(L, tmp_path, monkeypatch, n, native):
+    """after_load may close the handle, which owns the names: with the load on a
+    helper thread the views are whole all the same, and without one the call
+    fails as on any closed handle."""
+    spec = synth.tiny(54, n=n, alignment=16, max_bytes=64)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
+    want = [t.name for t in spec.tensors]
+    for threaded in (True, False):
+        monkeypatch.setattr(binding, "_THREADED_VIEWS_MIN", 0 if threaded else 1 << 30)
+        ck = binding.Checkpoint(str(tmp_path), index_only=True)
+        buf = torch.zeros(ck.total_bytes, dtype=torch.uint8)
+        if not native:
+            buf = buf.as_subclass(type("Buffer", (torch.Tensor,), {}))
+        monkeypatch.setattr(ck, "load_into", lambda buf, stream: None)
+        if threaded:
+            assert list(ck.load_with_views(buf, None, after_load=ck.close)) == want
+        else:
+            with pytest.raises(binding.SllmError) as ei:
+                ck.load_with_views(buf, None, after_load=ck.close)
+            assert ei.value.code == -1
+
+
+def test_errors_of_the_names_callback(L, tmp_path):
+    spec = synth.tiny(55, n=10, alignment=16)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
+
+    def bad():
+        raise KeyError("stop")
+
+    with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+        with pytest.raises(KeyError):
+            ck._views(torch.zeros(ck.total_bytes, dtype=torch.uint8), ck._table(), bad)
