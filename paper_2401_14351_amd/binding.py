@@ -62,11 +62,13 @@ class TensorInfo(C.Structure):
 
 
 # Below this many tensors load_with_views builds the views after the load call,
-# while the device still moves the last chunks (0.25-0.5 us a view).  A helper
-# thread costs about 0.1 ms: loads of 448 and 4,001 tensors cached in DRAM take
-# 0.76 and 2.87 ms without it, 0.84 and 2.95 ms with it; streams of 3,000 take
-# the same either way, and 2.3 GB in 10,000 tensors 46.1 against 41.2 ms.
+# while the device still moves the last chunks.  A helper thread costs about 0.1
+# ms, a view 0.25-0.5 us natively and about 3 us in the Python form.  Natively,
+# loads of 448 and 4,001 tensors cached in DRAM take 0.76 and 2.87 ms without
+# the thread, 0.84 and 2.95 ms with it; streams of 3,000 take the same either
+# way, and 2.3 GB in 10,000 tensors 46.1 against 41.2 ms.
 _THREADED_VIEWS_MIN = 8192
+_THREADED_PYTHON_VIEWS_MIN = 1024
 
 # the same layout as TensorInfo, for decoding a whole table with numpy
 _TENSOR_INFO = np.dtype([("name", "<u8"), ("dtype", "<u4"), ("ndim", "<u4"), ("shape", "<i8", (MAX_NDIM,)),
@@ -388,7 +390,8 @@ class Checkpoint:
         loading thread once the load is enqueued."""
         n = C.c_uint64()
         check(lib().sllm_tensor_index(self._h, None, 0, C.byref(n)))
-        if n.value < _THREADED_VIEWS_MIN:  # a helper thread costs more than these views
+        # few views cost less than a helper thread
+        if n.value < (_THREADED_VIEWS_MIN if _native_views_serve(buf) else _THREADED_PYTHON_VIEWS_MIN):
             self.load_into(buf, stream)
             if after_load is not None:
                 after_load()
@@ -422,13 +425,10 @@ class Checkpoint:
         return out
 
     def _views(self, buf, table, names_read: Optional[Callable[[], None]] = None):
-        """views(buf, self.tensors()), built natively from the index table.
-        A tensor subclass or a torch function mode sees the calls of the
-        Python form instead.  ``names_read`` is called once the table's names
-        are no longer needed."""
-        import torch
-
-        if type(buf) is not torch.Tensor or torch._C._len_torch_function_stack():
+        """views(buf, self.tensors()), built natively from the index table
+        where that serves.  ``names_read`` is called once the table's names are
+        no longer needed."""
+        if not _native_views_serve(buf):
             tensors = self.tensors()
             if names_read is not None:
                 names_read()
@@ -475,6 +475,22 @@ def _check_buffer(buf) -> None:
     if buf.dtype != torch.uint8 or buf.dim() != 1 or not buf.is_contiguous():
         raise ValueError(f"expected a contiguous 1-d uint8 tensor, got {buf.dtype} with shape "
                          f"{tuple(buf.shape)} and strides {buf.stride()}")
+
+
+def _native_views_serve(buf) -> bool:
+    """Whether the views of ``buf`` may be built natively: a tensor subclass or
+    a torch function mode must see the calls of the Python form.  The mode of
+    ``torch.device(...)`` and ``torch.set_default_device`` changes only calls
+    that make new tensors, so it needs to see none of them."""
+    import torch
+
+    if type(buf) is not torch.Tensor:
+        return False
+    if not torch._C._len_torch_function_stack():
+        return True
+    from torch.utils._device import DeviceContext
+
+    return all(type(m) is DeviceContext for m in torch.overrides._get_current_function_mode_stack())
 
 
 def views(buf, tensors: Sequence[Tensor]) -> Dict[str, object]:

@@ -86,7 +86,8 @@ def test_handle_closed_after_the_load(L, tmp_path, monkeypatch, n, native):
     binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
     want = [t.name for t in spec.tensors]
     for threaded in (True, False):
-        monkeypatch.setattr(binding, "_THREADED_VIEWS_MIN", 0 if threaded else 1 << 30)
+        for limit in ("_THREADED_VIEWS_MIN", "_THREADED_PYTHON_VIEWS_MIN"):
+            monkeypatch.setattr(binding, limit, 0 if threaded else 1 << 30, raising=False)
         ck = binding.Checkpoint(str(tmp_path), index_only=True)
         buf = torch.zeros(ck.total_bytes, dtype=torch.uint8)
         if not native:
@@ -110,3 +111,50 @@ def test_errors_of_the_names_callback(L, tmp_path):
     with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
         with pytest.raises(KeyError):
             ck._views(torch.zeros(ck.total_bytes, dtype=torch.uint8), ck._table(), bad)
+
+
+class Mode(torch.overrides.TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("where,native", [("plain", True), ("device", True), ("default device", True), ("nested", False),
+                                          ("mode", False), ("subclass", False)])
+def test_which_form_and_thread(L, tmp_path, monkeypatch, where, native):
+    """Under torch.device(...) and torch.set_default_device the views are built
+    natively; other function modes and subclasses get the Python form, for which
+    a helper thread pays from 1,024 tensors on."""
+    import threading
+
+    binding.convert(((f"t{i}", "i8", (0,), b"") for i in range(2000)), str(tmp_path), 16)
+    started, forms = [], []
+    monkeypatch.setattr(threading.Thread, "start", lambda self, start=threading.Thread.start: (started.append(self.name), start(self)))
+    monkeypatch.setattr(binding, "views", lambda *a, f=binding.views: (forms.append("python"), f(*a))[1])
+    with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+        monkeypatch.setattr(ck, "load_into", lambda buf, stream: None)
+        buf = torch.zeros(64, dtype=torch.uint8)
+        if where == "subclass":
+            buf = buf.as_subclass(type("Buffer", (torch.Tensor,), {}))
+
+        def go():
+            assert len(ck.load_with_views(buf)) == 2000
+
+        if where == "device":
+            with torch.device("cpu"):
+                go()
+        elif where == "default device":
+            torch.set_default_device("cpu")
+            try:
+                go()
+            finally:
+                torch.set_default_device(None)
+        elif where == "nested":
+            with torch.device("cpu"), Mode():
+                go()
+        elif where == "mode":
+            with Mode():
+                go()
+        else:
+            go()
+    assert forms == ([] if native else ["python"])
+    assert started == ([] if native else ["sllm-load"])
