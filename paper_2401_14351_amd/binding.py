@@ -177,14 +177,14 @@ def lib() -> C.CDLL:
 
 @functools.lru_cache(maxsize=None)
 def _views_ext():
-    """The native view builder (raises if it has not been built)."""
-    import torch  # noqa: F401  (its libraries resolve the extension's symbols)
-
+    """The native view builder, or None where it was not built for this Python
+    and torch: the views are then built in Python."""
     try:
+        import torch  # its libraries resolve the extension's symbols
         from paper_2401_14351_amd import _views
-    except ImportError as e:
-        raise RuntimeError("_views.so is missing or does not load: build it with python -m paper_2401_14351_amd.build") from e
-    return _views
+    except ImportError:
+        return None
+    return _views if torch.__version__.split("+")[0] == _views.TORCH_VERSION else None
 
 
 class SllmError(RuntimeError):
@@ -484,7 +484,7 @@ def _native_views_serve(buf) -> bool:
     that make new tensors, so it needs to see none of them."""
     import torch
 
-    if type(buf) is not torch.Tensor:
+    if type(buf) is not torch.Tensor or _views_ext() is None:
         return False
     if not torch._C._len_torch_function_stack():
         return True

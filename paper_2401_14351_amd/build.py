@@ -1,6 +1,7 @@
 """Build ``libsllm.so`` in-tree: the C++ host runtime and the gfx950 HIP kernels
-behind the C ABI declared in ``include/sllm.h``; and ``_views.so``, the Python
-binding's native view builder (the only part that knows torch).
+behind the C ABI declared in ``include/sllm.h``; and ``_views``, the Python
+binding's native view builder, the only part that knows torch: left out, with a
+note, where torch or its headers are not installed.
 
 Run ``python -m paper_2401_14351_amd.build`` (or ``__graft_entry__.build()``).
 """
@@ -11,6 +12,7 @@ import os
 import shlex
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -20,7 +22,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsllm.so")
 VIEWS_SRC = os.path.join(PKG, "pyext", "views.cpp")
-VIEWS = os.path.join(PKG, "_views.so")
+VIEWS = os.path.join(PKG, "_views" + sysconfig.get_config_var("EXT_SUFFIX"))  # names the Python it is for
 ARCH = "gfx950"
 
 # Every HIP compile leaves packed-FP32 instructions out of the generated code.
@@ -56,20 +58,24 @@ def _run(cmd, verbose):
 
 
 def views_command(out: str):
-    """The compiler call that makes the view builder for this interpreter and its torch."""
-    import sysconfig
-
-    import torch
-
+    """The compiler call that makes the view builder for this interpreter and
+    its torch, or None without torch's headers."""
+    try:
+        import torch
+    except ImportError:
+        return None
     base = os.path.dirname(os.path.abspath(torch.__file__))
     inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include")]
+    python = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(inc[0], "ATen", "Functions.h")) or not os.path.exists(os.path.join(python, "Python.h")):
+        return None
     return [_cxx(), "-shared", "-O2", "-fPIC", "-std=c++17", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-            f"-I{INCLUDE}", *[a for i in inc for a in ("-isystem", i)], f"-I{sysconfig.get_paths()['include']}", VIEWS_SRC,
+            f"-I{INCLUDE}", *[a for i in inc for a in ("-isystem", i)], f"-I{python}", VIEWS_SRC,
             "-o", out, f"-L{os.path.join(base, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source, link ``libsllm.so`` and ``_views.so``; return the former's path."""
+    """Compile every source, link ``libsllm.so`` and the view builder; return the former's path."""
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = []
     for src in sources():
@@ -80,14 +86,19 @@ def build(verbose: bool = False) -> str:
             cmd = [_cxx(), "-c", *COMMON, *HOST_FLAGS, src, "-o", obj]
         jobs.append((cmd, obj))
     views_tmp = VIEWS + ".tmp"
-    jobs.insert(0, (views_command(views_tmp), None))  # the longest one first
+    views = views_command(views_tmp)
+    if views:
+        jobs.insert(0, (views, None))  # the longest one first
+    else:
+        print("no torch headers: the view builder is left out, views are built in Python", flush=True)
     workers = max(1, min(len(jobs), os.cpu_count() or 1, 16))
     with ThreadPoolExecutor(workers) as ex:
         list(ex.map(lambda j: _run(j[0], verbose), jobs))
     tmp = LIB + ".tmp"
     _run([_hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", *[o for _, o in jobs if o], "-o", tmp, "-lpthread"], verbose)
     os.replace(tmp, LIB)
-    os.replace(views_tmp, VIEWS)
+    if views:
+        os.replace(views_tmp, VIEWS)
     return LIB
 
 

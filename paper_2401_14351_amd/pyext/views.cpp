@@ -14,6 +14,7 @@
 #include <ATen/Functions.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <algorithm>
 #include <cstdint>
@@ -96,4 +97,9 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_views", "Views over a loaded buf
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__views(void) { return PyModule_Create(&kModule); }
+// TORCH_VERSION lets the binding refuse a builder made for another torch.
+PyMODINIT_FUNC PyInit__views(void) {
+    PyObject* m = PyModule_Create(&kModule);
+    if (m && PyModule_AddStringConstant(m, "TORCH_VERSION", TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

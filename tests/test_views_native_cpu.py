@@ -18,6 +18,48 @@ def L():
     return binding.lib()
 
 
+def test_builder_is_built(L):
+    """What the other tests compare is the native form (it is optional otherwise)."""
+    assert binding._views_ext() is not None
+
+
+@pytest.mark.parametrize("why", ["missing", "another torch"])
+def test_without_the_builder(L, tmp_path, monkeypatch, why):
+    """Views are built in Python where the builder is missing or was made for
+    another Python or torch."""
+    import sys
+
+    import paper_2401_14351_amd as package
+
+    if why == "missing":
+        monkeypatch.setitem(sys.modules, "paper_2401_14351_amd._views", None)
+        monkeypatch.delattr(package, "_views", raising=False)
+    else:
+        monkeypatch.setattr(binding._views_ext(), "TORCH_VERSION", "1.0", raising=False)
+    binding._views_ext.cache_clear()
+    spec = synth.tiny(56, n=20, alignment=16)
+    binding.convert(((t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))), str(tmp_path), 16)
+    try:
+        with binding.Checkpoint(str(tmp_path), index_only=True) as ck:
+            monkeypatch.setattr(ck, "load_into", lambda buf, stream: None)
+            buf = torch.zeros(ck.total_bytes, dtype=torch.uint8)
+            assert binding._views_ext() is None
+            same(ck.load_with_views(buf), binding.views(buf, ck.tensors()))
+    finally:
+        monkeypatch.undo()
+        binding._views_ext.cache_clear()
+
+
+def test_library_builds_without_torch(monkeypatch):
+    """The view builder alone needs torch's headers."""
+    import sys
+
+    from paper_2401_14351_amd import build
+
+    monkeypatch.setitem(sys.modules, "torch", None)
+    assert build.views_command("x") is None
+
+
 def same(a, b):
     assert list(a) == list(b)
     for name in a:
