@@ -41,8 +41,8 @@
  *     A caller that resets a device must not use the library afterwards.
  *   - The device tables and HBM staging of a handle with a dev_alignment go
  *     back to the library at close and stay idle for the next handle (at most
- *     64 MiB in 32 blocks per device; more is freed, and the idle ones are
- *     freed when an allocation of theirs finds no memory).
+ *     256 MiB in 32 blocks per device; the oldest are freed beyond that, and
+ *     all of them when a handle's allocation finds no memory).
  *   - A load or repack may be captured into a HIP graph; the handle must stay
  *     open while the graph is replayed.  The device tables and staging of a
  *     handle used that way are freed at close, which waits for the device and

@@ -22,7 +22,8 @@ namespace sllm {
 // Device memory that outlives the handle that took it: a block given back stays
 // idle, up to kMaxIdleBlockBytes and kMaxIdleBlocks a device, for the next
 // handle, so opening and closing a handle per load costs no allocation and no
-// hipFree (which waits for the whole device).  A block may be given back once
+// hipFree (which waits for the whole device), unless its blocks do not fit
+// (copy-engine loads by sixteen streams or more).  A block may be given back once
 // no work uses it.  An allocation that fails frees the idle blocks and tries
 // again.  Safe from several threads.
 struct DeviceBlock {
@@ -30,7 +31,7 @@ struct DeviceBlock {
     uint8_t* p = nullptr;
     uint64_t bytes = 0;  // capacity
 };
-constexpr uint64_t kMaxIdleBlockBytes = 64ull << 20;
+constexpr uint64_t kMaxIdleBlockBytes = 256ull << 20;
 constexpr size_t kMaxIdleBlocks = 32;
 int32_t block_take(int device, uint64_t bytes, DeviceBlock* out);  // `device` is current
 void block_give(DeviceBlock* b);                                   // b's device is current

@@ -296,8 +296,21 @@ int32_t check_device_range(const void* p, uint64_t bytes, int device, const char
     return SLLM_OK;
 }
 
-// HBM staging of a copy stream at most (a copy-engine load into a device layout).
-constexpr uint64_t kStageBytes = 16ull << 20;
+// HBM staging of each copy stream for copy-engine loads into a device layout:
+// a chunk, for resident images merged runs of at least 64 MiB.  Up to two
+// streams take turns with the copy engine, and each piece then costs about 16
+// us of hand-over between engine and repack: 2.1 GB by two streams take 41.1 ms
+// in 16 MiB pieces, 39.8 in 32, 39.0 in 64 and 38.7 in 128; 250 MB 4.82, 4.68,
+// 4.56 and 4.52.  From three streams on they overlap (37.8 ms for any of these).
+// All streams' staging stays within 192 MiB, in pieces of 16 MiB at least, so
+// that with the tables it fits the idle blocks: opening and closing a handle
+// for each of the 250 MB loads takes 4.62 ms with kept blocks, 5.03 without.
+uint64_t stage_piece(uint64_t total, uint64_t chunk, bool resident, uint32_t n_streams) {
+    constexpr uint64_t kMerged = 64ull << 20, kAll = 192ull << 20, kLeast = 16ull << 20;
+    static_assert(kAll + (32ull << 20) <= kMaxIdleBlockBytes, "the tables fit beside the staging");
+    const uint64_t want = resident ? std::max(chunk, kMerged) : chunk;
+    return std::min({total, want, std::max(kAll / n_streams, kLeast)});
+}
 
 // Largest merged copy of a cached partition (SLLM_SDMA_MAX_COPY_MB, default
 // 256), read at every load so that one process can compare sizes.
@@ -723,13 +736,8 @@ extern "C" int32_t sllm_open(const char* dir, const sllm_open_opts* opts, sllm_c
         if (st != SLLM_OK) return bail(st);
     }
     if (h->dev_align) {
-        // copy-engine loads stage in HBM, one piece per stream at a time.  16 MiB
-        // pieces move as fast as 64 MiB ones, and two of them fit the idle
-        // blocks: OPT-125M cached, the default two streams, takes 4.60 ms a
-        // load where allocating and freeing 2 x 64 MiB each time took 4.95
-        // (8 MiB pieces: 4.64 to 5.4; 32 MiB: 4.72).
         const uint64_t staging = (h->engine == SLLM_ENGINE_SDMA) ? h->n_streams : 0;
-        const uint64_t stage_bytes = std::min<uint64_t>(h->cached || h->keep ? h->ix.total : h->chunk, kStageBytes);
+        const uint64_t stage_bytes = stage_piece(h->ix.total, h->chunk, h->cached || h->keep, h->n_streams);
         st = device_layout_build(h->ix, h->device, h->dev_off.data(), h->dev_total, h->dev_align, staging, stage_bytes,
                                  &h->layout);
         if (st != SLLM_OK) return bail(st);

@@ -185,7 +185,7 @@ def case_error_not_left_pending():
 
 
 def case_idle_blocks():
-    """Blocks of closed handles wait for the next one, at most 64 MiB in 32
+    """Blocks of closed handles wait for the next one, at most 256 MiB in 32
     blocks, the oldest given up first: sizes no handle takes any more do not
     keep later ones out."""
     small, large = convert("s", [100]), convert("l", [1] * 20_000)
@@ -212,9 +212,9 @@ def case_idle_blocks():
     big = convert("b", [20 * MiB], chunk=64 * KiB)
     with binding.Pool(64 * KiB, 320) as p2:
         p2.cache(big)
-        for n in (3, 1, 2):
+        for n in (10, 9, 8):
             binding.Checkpoint(big, pool=p2, dev_alignment=16, engine="sdma", n_streams=n, io_threads=1).close()
-            assert fake.fake_used() - base <= 64 * MiB
+            assert fake.fake_used() - base <= 256 * MiB
     assert reopened(ckpt_dir=large, dev_alignment=16) == 0
     # more than all idle blocks may hold: freed at once, without the others
     with binding.Pool(64 * KiB, 320) as p2:
@@ -246,6 +246,40 @@ def case_tables_are_checked():
     fake.fake_corrupt(NO_LIMIT)
     with binding.Checkpoint(d, dev_alignment=256, ring_slots=1):
         pass
+
+
+def case_staging_sizes():
+    """Copy-engine staging: a chunk for streams, merged runs of 64 MiB for
+    resident images, never more than the image, and what all streams of a
+    handle hold is kept with its tables below sixteen streams."""
+    d = convert("c", [100 * MiB + 5], chunk=MiB)
+    pool = binding.Pool(MiB, 101)
+    wide = binding.Pool(96 * MiB, 2)
+
+    def staging(pool, n, **opts):
+        before = fake.fake_used()
+        with binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=n, **opts):
+            held = fake.fake_used() - before
+        kept = fake.fake_used()
+        with binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=n, **opts):
+            again = fake.fake_used() - kept
+        fake.fake_limit(0)  # drop the idle blocks
+        try:
+            binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=64, **opts)
+        except binding.SllmError:
+            pass
+        fake.fake_limit(NO_LIMIT)
+        return held // MiB, again == 0
+
+    assert staging(pool, 2, ring_slots=4) == (2, True)  # streamed
+    assert staging(wide, 1, ring_slots=2) == (96, True)
+    pool.cache(d)
+    wide.cache(d)
+    for n, held in ((1, 64), (2, 128), (3, 192), (4, 192), (8, 192), (12, 192), (15, 240)):
+        assert staging(pool, n) == (held, True), n
+    assert staging(pool, 17) == (272, False)
+    assert staging(wide, 1) == (96, True)
+    assert staging(wide, 3) == (192, True)
 
 
 if __name__ == "__main__":

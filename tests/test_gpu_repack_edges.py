@@ -97,12 +97,14 @@ def test_noalloc_tables(tmp_path, monkeypatch, name):
         monkeypatch.delenv("SLLM_NOALLOC_PLAN_BLOCKS", raising=False)
 
 
+@pytest.mark.parametrize("streams", [2, 12])
 @pytest.mark.parametrize("C", [24 << 20, (17 << 20) + 24])
 @pytest.mark.parametrize("source", ["cached", "streamed", "keep"])
-def test_staging_pieces(tmp_path, C, source):
-    """Copy-engine loads into a device layout with chunks larger than a
-    stream's HBM staging (16 MiB), which go through it in pieces; two handles
-    in a row, the second on the device blocks the first gave back."""
+def test_staging_pieces(tmp_path, C, source, streams):
+    """Copy-engine loads into a device layout, with chunks no larger than a
+    stream's HBM staging (two streams) and larger than it (twelve: 16 MiB each),
+    which go through it in pieces; two handles in a row, the second on the
+    device blocks the first gave back."""
     import torch
 
     rng = np.random.default_rng(3)
@@ -112,13 +114,13 @@ def test_staging_pieces(tmp_path, C, source):
     index = oracle.make_index(tensors, 16, C)
     image = bytes(oracle.partition_bytes(tensors, 16)[:index.total_bytes])
     for A2 in (256, 4096):
-        print("[gpu-test] staging pieces", C, source, A2, flush=True)
+        print("[gpu-test] staging pieces", C, source, streams, A2, flush=True)
         want = np.frombuffer(bytes(oracle.repack(image, index, A2)), np.uint8)
         with binding.Pool(C, 2 if source == "streamed" else 4) as pool:
             if source == "cached":
                 pool.cache(str(tmp_path))
             with binding.Checkpoint(str(tmp_path), pool=pool, engine="sdma", dev_alignment=A2, ring_slots=2,
-                                    cache=source == "keep") as ck:
+                                    n_streams=streams, cache=source == "keep") as ck:
                 for rep in range(2):
                     dst = torch.full((len(want) + 64,), SENTINEL, dtype=torch.uint8, device="cuda:0")
                     ck.load_into(dst, torch.cuda.current_stream())
