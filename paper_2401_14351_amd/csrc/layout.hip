@@ -653,7 +653,7 @@ bool k2_two_kib(const DeviceLayout& l) {
 
 // Launch shape, read at every launch so that one process can compare shapes:
 // SLLM_K2_NT (streaming stores) and SLLM_K2_MAX_GRID (workgroups a launch)
-// for HBM sources; SLLM_K2_UNROLL (2, 4 or 8 vectors per lane) and
+// for HBM sources; SLLM_K2_UNROLL (8 vectors per lane, any other value 4) and
 // SLLM_K1_BLOCKS / SLLM_K1_STREAM_BLOCKS (grid of a launch that moves the
 // whole image / part of it, as for K1) for host sources.
 int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream_t stream, uint64_t plan0 = 0,
@@ -704,8 +704,9 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
     // full, and there a workgroup's pass over its tile counts: 8 KiB tiles (U = 2)
     // take 11 us against 31 on 64 KB, 18.5 / 36.4 on 0.5 MB, 47.6 / 50.2 on 2.1
     // MB, and from 10 MB on no less (42 MB 772 / 758).
-    const uint32_t knob = env_uint("SLLM_K2_UNROLL", a.table && a.y1 - a.y0 < (4u << 20) ? 2 : 8);
-    const uint32_t unroll = knob >= 8 ? 8 : knob >= 4 ? 4 : 2;
+    constexpr uint32_t kUnset = UINT32_MAX;
+    const uint32_t knob = env_uint("SLLM_K2_UNROLL", kUnset);
+    const uint32_t unroll = knob == kUnset ? (a.table && a.y1 - a.y0 < (4u << 20) ? 2 : 8) : knob >= 8 ? 8 : 4;
     const uint64_t tile = (uint64_t)kThreads * 16 * unroll;
     a.tile0 = a.y0 / tile;
     a.n_tiles = ceil_div(a.y1, tile) - a.tile0;
@@ -714,10 +715,10 @@ int32_t launch(const DeviceLayout& l, ScatterArgs a, bool src_is_host, hipStream
         1, a.table ? env_uint("SLLM_K1_BLOCKS", 512) : env_uint("SLLM_K1_STREAM_BLOCKS", 64));
     const dim3 grid((uint32_t)std::min<uint64_t>(a.n_tiles, want)), block(kThreads);
     auto run = [&](auto kernel) { kernel<<<grid, block, 0, stream>>>(a); };
-    auto pick = [&](auto k2, auto k4, auto k8) { run(unroll == 8 ? k8 : unroll == 4 ? k4 : k2); };
-    if (a.run_n) pick(k_scatter<2, false, kRun>, k_scatter<4, false, kRun>, k_scatter<8, false, kRun>);
-    else if (a.table) pick(k_scatter<2, false, kTable>, k_scatter<4, false, kTable>, k_scatter<8, false, kTable>);
-    else pick(k_scatter<2, false, kWindow>, k_scatter<4, false, kWindow>, k_scatter<8, false, kWindow>);
+    const bool u8 = unroll == 8;
+    if (a.run_n) run(u8 ? k_scatter<8, false, kRun> : k_scatter<4, false, kRun>);
+    else if (a.table) run(u8 ? k_scatter<8, false, kTable> : unroll == 4 ? k_scatter<4, false, kTable> : k_scatter<2, false, kTable>);
+    else run(u8 ? k_scatter<8, false, kWindow> : k_scatter<4, false, kWindow>);
     SLLM_HIP(hipGetLastError());
     return SLLM_OK;
 }

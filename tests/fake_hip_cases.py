@@ -17,6 +17,7 @@ for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_
               "fake_waits"):
     getattr(fake, _name).restype = C.c_uint64
 fake.fake_bad_list.restype = C.c_char_p
+fake.fake_last_kernel.restype = C.c_char_p
 fake.fake_limit.argtypes = [C.c_uint64]
 fake.fake_corrupt.argtypes = [C.c_uint64]
 fake.fake_fail_launch.argtypes = [C.c_int64]
@@ -280,6 +281,24 @@ def case_staging_sizes():
     assert staging(pool, 17) == (272, False)
     assert staging(wide, 1) == (96, True)
     assert staging(wide, 3) == (192, True)
+
+
+def case_scatter_unroll():
+    """Vectors per lane of cached loads into a device layout: 2 for images below
+    4 MiB, else 8; SLLM_K2_UNROLL gives 8, or 4 for any other value."""
+    for sizes, default in (([3 * MiB], 2), ([5 * MiB], 8)):
+        d = convert(f"c{default}", sizes, chunk=MiB)
+        n2 = total(sizes, 256)
+        dst = fake.fake_device_alloc(n2)
+        with binding.Pool(MiB, 8) as pool:
+            pool.cache(d)
+            with binding.Checkpoint(d, pool=pool, dev_alignment=256) as ck:
+                for knob, want in ((None, default), ("2", 4), ("4", 4), ("8", 8), ("16", 8), ("x", default)):
+                    os.environ.pop("SLLM_K2_UNROLL", None)
+                    if knob:
+                        os.environ["SLLM_K2_UNROLL"] = knob
+                    ck.load(dst, n2, fake.fake_stream())
+                    assert f"k_scatterILj{want}E".encode() in fake.fake_last_kernel(), (knob, fake.fake_last_kernel())
 
 
 if __name__ == "__main__":

@@ -36,6 +36,7 @@ int64_t fail_launch = -1;  // the launch after this many more fails
 std::string bad_calls;     // what was called on a capturing stream or a captured event
 hipError_t pending = hipSuccess;
 std::map<const void*, std::string> kernels;
+std::string last_kernel;
 struct {
     dim3 grid, block;
     size_t shmem;
@@ -78,6 +79,7 @@ void run_tables(const sllm::TableArgs& a) {
 
 hipError_t launched(const void* f, void** args) {
     ++n_launch;
+    last_kernel = kernels[f];
     if (fail_launch == 0) {
         fail_launch = -1;
         return err(hipErrorLaunchFailure);
@@ -100,6 +102,7 @@ uint64_t fake_records_captured() { return n_record_captured; }
 uint64_t fake_waits() { return n_wait; }
 uint64_t fake_bad_calls() { return n_bad_calls; }
 const char* fake_bad_list() { return bad_calls.c_str(); }
+const char* fake_last_kernel() { return last_kernel.c_str(); }
 int fake_pending() { return (int)pending; }
 void fake_limit(uint64_t bytes) { device_limit = bytes; }
 void fake_fail_launch(int64_t after) { fail_launch = after; }
