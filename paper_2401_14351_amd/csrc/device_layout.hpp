@@ -23,7 +23,7 @@ namespace sllm {
 // idle, up to kMaxIdleBlockBytes and kMaxIdleBlocks a device, for the next
 // handle, so opening and closing a handle per load costs no allocation and no
 // hipFree (which waits for the whole device), unless its blocks do not fit
-// (copy-engine loads by sixteen streams or more).  A block may be given back once
+// (the staging of large copy-engine loads by four streams or more).  A block may be given back once
 // no work uses it.  An allocation that fails frees the idle blocks and tries
 // again.  Safe from several threads.
 struct DeviceBlock {

@@ -301,15 +301,18 @@ int32_t check_device_range(const void* p, uint64_t bytes, int device, const char
 // streams take turns with the copy engine, and each piece then costs about 16
 // us of hand-over between engine and repack: 2.1 GB by two streams take 41.1 ms
 // in 16 MiB pieces, 39.8 in 32, 39.0 in 64 and 38.7 in 128; 250 MB 4.82, 4.68,
-// 4.56 and 4.52.  From three streams on they overlap (37.8 ms for any of these).
-// All streams' staging stays within 192 MiB, in pieces of 16 MiB at least, so
-// that with the tables it fits the idle blocks: opening and closing a handle
-// for each of the 250 MB loads takes 4.62 ms with kept blocks, 5.03 without.
+// 4.56 and 4.52.  From three streams on they overlap (2.1 GB 37.8 ms in any of
+// these).  So that the idle blocks can keep it with the tables, all streams'
+// staging together holds 192 MiB, or the image, in up to 64 MiB each, where
+// that is more: opening and closing a handle for each load of 250 MB takes 4.62
+// ms with two streams (5.03 where it is allocated each time) and 4.54 with
+// eight (5.33), and 2.1 GB by sixteen gain from the larger pieces (38.3 ms in
+// 16 MiB, 37.9 in 64).
 uint64_t stage_piece(uint64_t total, uint64_t chunk, bool resident, uint32_t n_streams) {
-    constexpr uint64_t kMerged = 64ull << 20, kAll = 192ull << 20, kLeast = 16ull << 20;
+    constexpr uint64_t kMerged = 64ull << 20, kAll = 192ull << 20, kLeast = 4ull << 20;
     static_assert(kAll + (32ull << 20) <= kMaxIdleBlockBytes, "the tables fit beside the staging");
     const uint64_t want = resident ? std::max(chunk, kMerged) : chunk;
-    return std::min({total, want, std::max(kAll / n_streams, kLeast)});
+    return std::min({total, want, std::max({kAll / n_streams, std::min(total / n_streams, kMerged), kLeast})});
 }
 
 // Largest merged copy of a cached partition (SLLM_SDMA_MAX_COPY_MB, default

@@ -249,15 +249,32 @@ def case_tables_are_checked():
         pass
 
 
+def sparse(name, sizes, A, chunk):
+    """A converted checkpoint whose data file has no blocks."""
+    import oracle
+
+    offsets, t = oracle.plan_layout(sizes, A)
+    entries = tuple(oracle.Entry(f"t{i}", "i8", (n,), 0, o, n) for i, (n, o) in enumerate(zip(sizes, offsets)))
+    index = oracle.Index(A, chunk, t, oracle.file_length(t), entries)
+    d = os.path.join(sys.argv[3], name)
+    os.mkdir(d)
+    with open(os.path.join(d, "sllm.index"), "wb") as f:
+        f.write(oracle.encode_index(index))
+    with open(os.path.join(d, "sllm.part0"), "wb") as f:
+        f.truncate(index.file_bytes)
+    return d
+
+
 def case_staging_sizes():
     """Copy-engine staging: a chunk for streams, merged runs of 64 MiB for
-    resident images, never more than the image, and what all streams of a
-    handle hold is kept with its tables below sixteen streams."""
-    d = convert("c", [100 * MiB + 5], chunk=MiB)
+    resident images, never more than the image; all streams' together 192 MiB,
+    or the image in up to 64 MiB each, and kept with the tables up to 256."""
+    d = sparse("c", [100 * MiB + 5], 16, MiB)
+    large = sparse("l", [1200 * MiB], 16, 16 * MiB)
     pool = binding.Pool(MiB, 101)
     wide = binding.Pool(96 * MiB, 2)
 
-    def staging(pool, n, **opts):
+    def staging(pool, n, d=d, **opts):
         before = fake.fake_used()
         with binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=n, **opts):
             held = fake.fake_used() - before
@@ -266,21 +283,24 @@ def case_staging_sizes():
             again = fake.fake_used() - kept
         fake.fake_limit(0)  # drop the idle blocks
         try:
-            binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=64, **opts)
+            binding.Checkpoint(d, pool=pool, engine="sdma", dev_alignment=16, n_streams=1 << 20, **opts)
         except binding.SllmError:
             pass
         fake.fake_limit(NO_LIMIT)
-        return held // MiB, again == 0
+        return held // MiB, again < 64 * KiB  # SLLM_OPEN_CACHE has a small table of its own
 
     assert staging(pool, 2, ring_slots=4) == (2, True)  # streamed
     assert staging(wide, 1, ring_slots=2) == (96, True)
     pool.cache(d)
     wide.cache(d)
-    for n, held in ((1, 64), (2, 128), (3, 192), (4, 192), (8, 192), (12, 192), (15, 240)):
+    for n, held in ((1, 64), (2, 128), (3, 192), (4, 192), (8, 192), (12, 192), (24, 192), (48, 192)):
         assert staging(pool, n) == (held, True), n
-    assert staging(pool, 17) == (272, False)
+    assert staging(pool, 100) == (400, False)
     assert staging(wide, 1) == (96, True)
     assert staging(wide, 3) == (192, True)
+    with binding.Pool(16 * MiB, 75) as p3:
+        for n, held in ((1, 64), (2, 128), (3, 192), (4, 256), (16, 1024), (24, 1200)):
+            assert staging(p3, n, large, cache=True) == (held, held < 256), n
 
 
 def case_scatter_unroll():
