@@ -321,6 +321,37 @@ def case_scatter_unroll():
                     assert f"k_scatterILj{want}E".encode() in fake.fake_last_kernel(), (knob, fake.fake_last_kernel())
 
 
+def case_pack_sizes():
+    """Sizes packed into kernel arguments and unpacked again, at every width and
+    every shift it leaves room for, with counts just below, at and above a
+    batch's capacity."""
+    rng = np.random.default_rng(1)
+    u64 = C.POINTER(C.c_uint64)
+    fake.fake_pack.restype = C.c_uint64
+    fake.fake_pack.argtypes = [u64, C.c_uint64, u64, u64, u64]
+
+    def pack(s):
+        s = np.ascontiguousarray(s, dtype=np.uint64)
+        out, counts, widths = np.zeros_like(s), np.zeros_like(s), np.zeros_like(s)
+        k = fake.fake_pack(*(a.ctypes.data_as(u64) if isinstance(a, np.ndarray) else a for a in (s, len(s), out, counts, widths)))
+        assert np.array_equal(out, s)
+        return counts[:k].tolist(), widths[:k].tolist()
+
+    for width in range(65):
+        most = min(2048, 31744 // width) if width else 2048
+        for shift in range(65 - width if width else 1):
+            top = (1 << width) - 1  # odd, so the shift is exact
+            base = int(rng.integers(0, (1 << 64) - (top << shift), dtype=np.uint64, endpoint=False)) if width + shift < 64 else 0
+            for n in (most - 1, most, most + 1):
+                v = rng.integers(0, top, n, dtype=np.uint64, endpoint=True) if top else np.zeros(n, np.uint64)
+                v[0], v[-2 if n > most else -1] = 0, top
+                counts, widths = pack((v << np.uint64(shift)) + np.uint64(base))
+                assert counts[0] == min(n, most) and sum(counts) == n, (width, shift, n, counts)
+                assert widths[0] == width, (width, shift, n, widths)
+    for n in (1, 2, 3, 5000):
+        pack(rng.integers(0, 1 << 40, n, dtype=np.uint64))
+
+
 if __name__ == "__main__":
     globals()["case_" + sys.argv[2]]()
     print("ok")

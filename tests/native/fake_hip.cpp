@@ -114,6 +114,20 @@ void* fake_device_alloc(uint64_t n) {
     return hipMalloc(&p, n) == hipSuccess ? p : nullptr;
 }
 
+// The n sizes packed and unpacked batch by batch; each batch's count and width.
+uint64_t fake_pack(const uint64_t* s, uint64_t n, uint64_t* unpacked, uint64_t* counts, uint64_t* widths) {
+    uint64_t batches = 0;
+    sllm::TableArgs a{};
+    for (uint64_t i = 0; i < n; i += a.m, ++batches) {
+        std::memset(a.words, 0xA5, sizeof a.words);  // an earlier batch's
+        a.m = sllm::pack_sizes(s + i, n - i, &a);
+        counts[batches] = a.m;
+        widths[batches] = a.width;
+        for (uint32_t j = 0; j < a.m; ++j) unpacked[i + j] = sllm::table_size(a, j);
+    }
+    return batches;
+}
+
 // ---- memory -------------------------------------------------------------------
 hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;

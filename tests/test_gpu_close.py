@@ -98,7 +98,8 @@ def test_close_waits_for_a_repack(torch_cuda, tmp_path):
 @pytest.mark.parametrize("grid", [None, "997"])
 def test_close_waits_for_repacks_on_two_streams(torch_cuda, tmp_path, monkeypatch, grid):
     """More repacks in flight than end events looked at per call, on two
-    streams, whole and split into several launches (the end rides on the last)."""
+    streams, whole and split into several launches (the end rides on the last).
+    Long copies ahead of them keep all of them waiting until close."""
     torch = torch_cuda
     if grid:
         monkeypatch.setenv("SLLM_K2_MAX_GRID", grid)
@@ -112,10 +113,18 @@ def test_close_waits_for_repacks_on_two_streams(torch_cuda, tmp_path, monkeypatc
     src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     outs = [torch.full((len(want),), 0xA5, dtype=torch.uint8, device="cuda:0") for _ in streams]
+    ahead = [torch.zeros(4 << 30, dtype=torch.uint8, device="cuda:0") for _ in range(2)]
     torch.cuda.synchronize()
     ck = binding.Checkpoint(d, dev_alignment=256)
+    ck.repack(src, outs[0], streams[0])  # the first call's own costs
+    torch.cuda.synchronize()
+    for s in streams:
+        with torch.cuda.stream(s):
+            for _ in range(30):  # 1.5 ms or more each
+                ahead[0].copy_(ahead[1])
     for i in range(60):
         ck.repack(src, outs[i % 2], streams[i % 2])
+    assert not any(s.query() for s in streams), "the copies ended too soon to show anything"
     ck.close()
     assert all(s.query() for s in streams), "close returned while a repack still ran"
     for o in outs:

@@ -1,9 +1,10 @@
 """The HBM repack at the edges of its tiles: slots that end a byte before,
 at and after a wave's kilobyte, a tile (8 KiB) and a plan block (16 KiB), runs
 of zero-size tensors longer than the 64 entries a wave loads at a time, and
-launches split so that they start and end inside plan blocks; and the size
-tables of the allocation-free repack at every width they are packed in.  Byte
-for byte against the oracle."""
+launches split so that they start and end inside plan blocks; the tables of the
+allocation-free repack around the ends of their batches, with the plan written
+in both ways; and the tables of an open at many widths of the packed sizes.
+Byte for byte against the oracle."""
 
 import numpy as np
 import pytest
@@ -60,15 +61,29 @@ def test_repack_edges(tmp_path, monkeypatch, A, grid, large):
             assert (got[len(want):] == SENTINEL).all(), "bytes past the image were written"
 
 
+def bits16(n):
+    """n sizes that pack into 16 bits each, 1,984 to a batch."""
+    sizes = [1 + (i * 40503) % 4999 + (60_000 if i % 900 == 0 else 0) for i in range(n)]
+    assert (max(sizes) - min(sizes)).bit_length() == 16
+    return sizes
+
+
 # sizes of n tensors: all equal (no bits), multiples of a power of two, one
-# large among small (wide values), and batch ends at 1,988 and 2,048 tensors
+# large among small (wide values), batch ends at 1,984 (16 bits) and 2,048
+# tensors, and batches, the last of them partial, whose plan is spread over the
+# grid (more than 4 blocks of 16 KiB a tensor)
 TABLES = {
     "equal": [513] * 2049,
     "shifted": [4096 * (1 + i % 5) for i in range(700)],
     "wide": [(i * 7919) % 301 for i in range(2500)] + [(9 << 20) + 5] + [i % 3 for i in range(40)],
-    "16 bits": [1 + (i * 40503) % 4999 + (65000 if i % 900 == 0 else 0) for i in range(1990)],
+    "16 bits, a batch less one": bits16(1983),
+    "16 bits, a batch": bits16(1984),
+    "16 bits, two batches": bits16(1990),
     "one": [77],
     "zeros": [0] * 2047 + [3, 0, 0],
+    "spread": bits16(1984) + [i % 700 for i in range(90)] + [(40 << 20) + 3] + [0, 5000, 16384],
+    "spread first": [(36 << 20) + 1] + [(i * 7919) % 301 for i in range(400)],
+    "spread, then not": [(1 << 18) - (i * 4099) % 30_000 for i in range(200)] + [(36 << 20) + 1] + [0] * 2000 + [77] * 60,
 }
 
 
@@ -153,3 +168,29 @@ def test_open_after_a_failed_allocation(tmp_path):
             torch.cuda.synchronize()
         assert np.array_equal(dst.cpu().numpy()[:len(want)], want)
         pool.evict(str(tmp_path))
+
+
+@pytest.mark.parametrize("width", [1, 2, 15, 16, 17, 24, 31, 32, 33])
+def test_tables_of_every_width(tmp_path, width):
+    """The tables an open computes, from sizes packed into `width` bits with
+    counts just below, at and above a batch's capacity, are those of the host:
+    open compares them, entry by entry.  The files are sparse, and no data is
+    read."""
+    most = min(2048, 31744 // width)
+    rng = np.random.default_rng(width)
+    for n in (most - 1, most, most + 1):
+        print("[gpu-test] tables of width", width, n, flush=True)
+        sizes = [int(x) for x in rng.integers(0, 1 << min(width, 12), n)]
+        sizes[0], sizes[-1] = 0, (1 << width) - 1
+        offsets, total = oracle.plan_layout(sizes, 64)
+        entries = tuple(oracle.Entry(f"t{i}", "i8", (x,), 0, o, x) for i, (x, o) in enumerate(zip(sizes, offsets)))
+        index = oracle.Index(64, 1 << 20, total, oracle.file_length(total), entries)
+        d = tmp_path / str(n)
+        d.mkdir()
+        (d / "sllm.index").write_bytes(oracle.encode_index(index))
+        with open(d / "sllm.part0", "wb") as f:
+            f.truncate(index.file_bytes)
+        for A2 in (16, 4096):
+            with binding.Checkpoint(str(d), dev_alignment=A2, ring_slots=1) as ck:
+                offsets2, total2 = oracle.device_layout(index, A2)
+                assert ck.total_bytes == total2 and [t.offset for t in ck.tensors()] == offsets2
