@@ -184,7 +184,7 @@ def _views_ext():
         from paper_2401_14351_amd import _views
     except ImportError:
         return None
-    return _views if torch.__version__.split("+")[0] == _views.TORCH_VERSION else None
+    return _views if torch.__version__.split("+")[0] == getattr(_views, "TORCH_VERSION", None) else None
 
 
 class SllmError(RuntimeError):

@@ -23,7 +23,7 @@ def test_builder_is_built(L):
     assert binding._views_ext() is not None
 
 
-@pytest.mark.parametrize("why", ["missing", "another torch"])
+@pytest.mark.parametrize("why", ["missing", "another torch", "no torch named"])
 def test_without_the_builder(L, tmp_path, monkeypatch, why):
     """Views are built in Python where the builder is missing or was made for
     another Python or torch."""
@@ -34,6 +34,8 @@ def test_without_the_builder(L, tmp_path, monkeypatch, why):
     if why == "missing":
         monkeypatch.setitem(sys.modules, "paper_2401_14351_amd._views", None)
         monkeypatch.delattr(package, "_views", raising=False)
+    elif why == "no torch named":  # a builder from before it named its torch
+        monkeypatch.delattr(binding._views_ext(), "TORCH_VERSION")
     else:
         monkeypatch.setattr(binding._views_ext(), "TORCH_VERSION", "1.0", raising=False)
     binding._views_ext.cache_clear()
