@@ -23,9 +23,9 @@ namespace sllm {
 // idle, up to kMaxIdleBlockBytes and kMaxIdleBlocks a device, for the next
 // handle, so opening and closing a handle per load costs no allocation and no
 // hipFree (which waits for the whole device), unless its blocks do not fit
-// (the staging of large copy-engine loads by four streams or more).  A block may be given back once
-// no work uses it.  An allocation that fails frees the idle blocks and tries
-// again.  Safe from several threads.
+// (the staging of large copy-engine loads by four streams or more).  A block may
+// be given back once no work uses it.  An allocation that fails frees the idle
+// blocks and tries again.  Safe from several threads.
 struct DeviceBlock {
     int device = 0;
     uint8_t* p = nullptr;
@@ -55,12 +55,12 @@ struct DeviceLayout {
 };
 
 // K2 from HBM moves the device image in tiles of kTileBytes (one 16-byte
-// vector for each of kK2Lanes lanes) or twice that, one per workgroup.  Its plan holds, for
-// each block of kPlanBytes, the shift o_m - d_m from a destination byte to its
-// partition byte when the block lies inside the data bytes of one tensor m,
-// or kMixedTile + m when it meets a boundary or padding and its first byte
-// lies in the slot of tensor m (entries below kMixedEnd: a shift is at most
-// the size of an image).
+// vector for each of kK2Lanes lanes) or twice that, one per workgroup.  Its plan
+// holds, for each block of kPlanBytes, the shift o_m - d_m from a destination
+// byte to its partition byte when the block lies inside the data bytes of one
+// tensor m, or kMixedTile + m when it meets a boundary or padding and its first
+// byte lies in the slot of tensor m (entries below kMixedEnd: a shift is at
+// most the size of an image).
 constexpr uint32_t kK2Lanes = 512;
 constexpr uint64_t kTileBytes = (uint64_t)kK2Lanes * 16;
 constexpr uint64_t kPlanBytes = 16384;

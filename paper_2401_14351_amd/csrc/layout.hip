@@ -13,11 +13,11 @@
 // K1-scatter (mapped pinned host source): each workgroup walks a span of
 //     tiles, finds the tensors whose slots meet a tile (a forward search of
 //     d), stages those index entries in LDS and keeps them for the following
-//     tiles they still cover; every lane
-//     produces aligned 16-byte destination vectors: a straight 16-byte load
-//     when source and destination agree mod 16, two aligned loads and a byte
-//     funnel shift when they do not, zeros for padding.  Only vectors cut by
-//     the window's first or last destination byte are written byte by byte.
+//     tiles they still cover; every lane produces aligned 16-byte destination
+//     vectors: a straight 16-byte load when source and destination agree mod
+//     16, two aligned loads and a byte funnel shift when they do not, zeros for
+//     padding.  Only vectors cut by the window's first or last destination byte
+//     are written byte by byte.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -94,9 +94,9 @@ constexpr uint64_t kTableBlocksEach = 4;
 // tensors of 256 B to 64 KiB need 11 launches of these (16 bits a size), where
 // 256 64-bit sizes a launch, a scan kernel per layout and a plan kernel took
 // 82: the repack they prepare went from 336 to 139 us, and to 134 with the plan
-// from registers and no second barrier.  Of a launch's 5.3 us
-// by bisection, 2.0 were the launch and its arguments, 0.6 the sizes, 1.3 the
-// scans and 1.4 the plan.
+// from registers and no second barrier.  Of a launch's 5.3 us by bisection, 2.0
+// were the launch and its arguments, 0.6 the sizes, 1.3 the scans and 1.4 the
+// plan.
 __global__ __launch_bounds__(1024) void k3_tables(TableArgs a) {
     __shared__ uint64_t s_dev[kTableBatch], s_off[kTableBatch], s_size[kTableBatch];
     __shared__ uint64_t tot_o[16], tot_d[16];

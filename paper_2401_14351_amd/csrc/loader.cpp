@@ -848,8 +848,9 @@ extern "C" int32_t sllm_repack(const sllm_ckpt* h, const void* src_dev, uint64_t
     uint8_t* dst = static_cast<uint8_t*>(dst_dev);
     const uint8_t* src = static_cast<const uint8_t*>(src_dev);
     // The end event rides on the kernel: a recorded event is a packet of its own
-    // with a system-scope fence, 2.6 us on the stream after each repack (40 MB
-    // in and out: 10.4 -> 7.8 us a repack).
+    // with a system-scope fence, 2 us on the stream after each repack (40 MB in
+    // and out, 200 in a row: 9.4 us each with it, 7.4 without).  A single repack
+    // that is waited for takes 2 us longer so (19.5 against 17.6).
     const bool capturing = is_capturing(s);
     if (capturing) h->captured = true;
     hipEvent_t end = nullptr;
