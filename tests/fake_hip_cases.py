@@ -14,7 +14,7 @@ sys.modules["torch"] = None  # "import torch" raises ImportError
 
 fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 for _name in ("fake_mallocs", "fake_frees", "fake_launches", "fake_used", "fake_records_captured", "fake_bad_calls",
-              "fake_waits"):
+              "fake_waits", "fake_spread"):
     getattr(fake, _name).restype = C.c_uint64
 fake.fake_bad_list.restype = C.c_char_p
 fake.fake_last_kernel.restype = C.c_char_p
@@ -350,6 +350,27 @@ def case_pack_sizes():
                 assert widths[0] == width, (width, shift, n, widths)
     for n in (1, 2, 3, 5000):
         pack(rng.integers(0, 1 << 40, n, dtype=np.uint64))
+
+
+def case_plan_writers():
+    """Which writer a batch's plan gets: spread over a grid beyond four blocks of
+    16 KiB a tensor, and from one on where more than 4 % of the tensors hold
+    more than eight; and no empty grid where a window ends in or before a batch."""
+    small, wide = 14 * KiB, 144 * KiB
+    for sizes, spread in (([64 * KiB] * 1000, 0), ([64 * KiB] * 1000 + [3 * MiB], 1),
+                          ([wide] * 40 + [small] * 960, 0), ([wide] * 41 + [small] * 959, 1),
+                          ([wide] * 41 + [256] * 959, 0), ([128 * KiB] * 100 + [small] * 900, 0),
+                          ([wide] * 2048 + [77] * 30 + [small] * 2018, 1), ([0] * 50, 0)):
+        d = sparse(f"c{len(sizes)}-{sizes.count(wide)}-{sum(sizes)}", sizes, 16, MiB)
+        before = fake.fake_spread()
+        with binding.Checkpoint(d, dev_alignment=16, ring_slots=1):
+            assert fake.fake_spread() - before == spread, (len(sizes), spread)
+        buf = Buffers(sizes, 16, 16)
+        with binding.Checkpoint(d, index_only=True) as ck:
+            for window in ("1", "1001", "5000"):
+                os.environ["SLLM_NOALLOC_PLAN_BLOCKS"] = window
+                st = binding.lib().sllm_repack_noalloc(ck._h, 16, buf.src, buf.n, buf.dst, buf.n2, fake.fake_stream())
+                assert st == 0 or buf.n2 == 0, (window, binding.lib().sllm_last_error())
 
 
 if __name__ == "__main__":

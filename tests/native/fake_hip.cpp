@@ -2,10 +2,10 @@
 // are memcpy, kernels are logged and not run, and events complete at once.
 // Loaded before libsllm.so with global symbols, it takes the place of the real
 // runtime for that library.  The index-table kernel alone is carried out, from
-// its arguments, since the host reads the tables back.  It keeps what the tests assert on: which blocks
-// were allocated and freed, what was called on a capturing stream or on an
-// event of a capture, and the error that stays pending until hipGetLastError.
-// Calls can be told to fail.
+// its arguments, since the host reads the tables back.  It keeps what the tests
+// assert on: which blocks were allocated and freed, what was called on a
+// capturing stream or on an event of a capture, and the error that stays pending
+// until hipGetLastError.  Calls can be told to fail.
 #define __HIP_PLATFORM_AMD__
 #include <hip/hip_runtime_api.h>
 
@@ -29,7 +29,7 @@ struct ihipEvent_t {
 namespace {
 
 std::map<uintptr_t, size_t> device_mem;
-uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls, n_wait;
+uint64_t n_malloc, n_free, n_launch, n_record_captured, n_bad_calls, n_wait, n_spread;
 uint64_t device_limit = UINT64_MAX, device_used;
 uint64_t corrupt = UINT64_MAX;  // 3 i + {0, 1, 2}: the table kernel writes a wrong o, d or s of tensor i
 int64_t fail_launch = -1;  // the launch after this many more fails
@@ -58,6 +58,7 @@ hipError_t bad(const char* what, hipError_t e) {
 
 // the index-table kernel's work, one tensor after another
 void run_tables(const sllm::TableArgs& a) {
+    n_spread += a.spread;
     uint64_t o = a.o0, d = a.d0;
     for (uint32_t j = 0; j < a.m; ++j) {
         const uint64_t s = sllm::table_size(a, j), i = a.i0 + j;
@@ -100,6 +101,7 @@ uint64_t fake_launches() { return n_launch; }
 uint64_t fake_used() { return device_used; }
 uint64_t fake_records_captured() { return n_record_captured; }
 uint64_t fake_waits() { return n_wait; }
+uint64_t fake_spread() { return n_spread; }  // table launches whose plan is spread over the grid
 uint64_t fake_bad_calls() { return n_bad_calls; }
 const char* fake_bad_list() { return bad_calls.c_str(); }
 const char* fake_last_kernel() { return last_kernel.c_str(); }
@@ -267,7 +269,9 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hip
     *s = call.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) { return launched(f, args); }
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
+    return grid.x ? launched(f, args) : err(hipErrorInvalidConfiguration);
+}
 hipError_t hipExtLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s, hipEvent_t, hipEvent_t end,
                               int) {
     if (end && capturing(s)) return bad("hipExtLaunchKernel with an event", hipErrorStreamCaptureUnsupported);

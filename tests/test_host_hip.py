@@ -37,6 +37,6 @@ def run(fake, tmp_path, case):
 
 @pytest.mark.parametrize("case", ["events_under_capture", "close_after_capture", "failure_under_capture",
                                   "error_not_left_pending", "idle_blocks", "tables_are_checked",
-                                  "staging_sizes", "scatter_unroll", "pack_sizes"])
+                                  "staging_sizes", "scatter_unroll", "pack_sizes", "plan_writers"])
 def test_host_code(fake, tmp_path, case):
     run(fake, tmp_path, case)
