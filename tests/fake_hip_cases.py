@@ -126,6 +126,23 @@ def case_close_after_capture():
             assert frees(engine, work) == 0, (engine, work)
 
 
+def case_open_under_capture():
+    """While another stream captures, a handle opens on idle blocks by no call
+    that would end the capture, and closes the same way."""
+    d = convert("c", SIZES)
+    s = fake.fake_stream()
+    pool = binding.Pool(64 * KiB, 32)
+    pool.cache(d)
+    for engine in ("kernel", "sdma"):
+        opts = {"pool": pool, "dev_alignment": 256, "engine": engine}
+        binding.Checkpoint(d, **opts).close()
+        fake.fake_capture(s, 1)
+        binding.Checkpoint(d, **opts).close()
+        fake.fake_capture(s, 0)
+        assert fake.fake_bad_calls() == 0, fake.fake_bad_list()
+        assert fake.fake_pending() == 0
+
+
 def case_failure_under_capture():
     """A repack or load that fails under capture returns its error and makes no
     call that HIP refuses on a capturing stream; eagerly it waits for the stream."""

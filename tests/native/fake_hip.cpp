@@ -49,6 +49,7 @@ hipError_t err(hipError_t e) {
 }
 
 bool capturing(hipStream_t s) { return s && s->capturing; }
+int n_capturing;  // streams the test put in capture
 
 hipError_t bad(const char* what, hipError_t e) {
     ++n_bad_calls;
@@ -110,7 +111,11 @@ void fake_limit(uint64_t bytes) { device_limit = bytes; }
 void fake_fail_launch(int64_t after) { fail_launch = after; }
 void fake_corrupt(uint64_t what) { corrupt = what; }
 void* fake_stream() { return new ihipStream_t; }
-void fake_capture(void* s, int on) { static_cast<ihipStream_t*>(s)->capturing = on != 0; }
+void fake_capture(void* s, int on) {
+    bool& now = static_cast<ihipStream_t*>(s)->capturing;
+    n_capturing += (on != 0) - now;
+    now = on != 0;
+}
 void* fake_device_alloc(uint64_t n) {
     void* p = nullptr;
     return hipMalloc(&p, n) == hipSuccess ? p : nullptr;
@@ -133,6 +138,7 @@ uint64_t fake_pack(const uint64_t* s, uint64_t n, uint64_t* unpacked, uint64_t* 
 // ---- memory -------------------------------------------------------------------
 hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;
+    if (n_capturing) return bad("hipMalloc", hipErrorStreamCaptureUnsupported);
     if (n > device_limit || device_used > device_limit - n) return err(hipErrorOutOfMemory);
     *p = std::aligned_alloc(4096, (n + 4095) / 4096 * 4096);
     device_mem[(uintptr_t)*p] = n;
@@ -181,6 +187,7 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* n, hipDeviceptr_t
     return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+    if (n_capturing) return bad("hipMemcpy", hipErrorStreamCaptureImplicit);
     std::memcpy(d, s, n);
     return hipSuccess;
 }

@@ -164,6 +164,43 @@ def test_repack_captured_in_a_graph(torch_cuda, tmp_path):
         del g
 
 
+def test_open_while_another_stream_captures(torch_cuda, tmp_path):
+    """A handle that opens on idle blocks, while a stream captures, leaves the
+    capture whole, and loads as ever."""
+    torch = torch_cuda
+    spec = synth.stress(n=60, max_bytes=256 << 10, seed=47)
+    tensors = [(t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))]
+    d = str(tmp_path / "open")
+    binding.convert(iter(tensors), d, 4096, 1 << 20)
+    index = oracle.make_index(tensors, 4096, 1 << 20)
+    want = bytes(oracle.repack(bytes(oracle.partition_bytes(tensors, 4096)[:index.total_bytes]), index, 256))
+    out = torch.zeros(len(want), dtype=torch.uint8, device="cuda:0")
+    x = torch.zeros(1 << 16, device="cuda:0")
+    y = torch.zeros_like(x)
+    side = torch.cuda.Stream()
+    with binding.Pool(1 << 20, -(-index.total_bytes // (1 << 20))) as pool:
+        pool.cache(d)
+        binding.Checkpoint(d, pool=pool, dev_alignment=256).close()  # its blocks stay idle
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            y.copy_(x)
+            ck = binding.Checkpoint(d, pool=pool, dev_alignment=256)
+            y.add_(1)
+        ck.load_into(out, side)
+        torch.cuda.synchronize()
+        assert out.cpu().numpy().tobytes() == want
+        for k in range(3):
+            x.fill_(k)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert (y == k + 1).all(), k
+        ck.close()
+        del g
+        pool.evict(d)
+
+
 @pytest.mark.parametrize("what", ["repack", "load"])
 def test_close_waits_for_replays(torch_cuda, tmp_path, what):
     """A captured repack, or cached load into a device layout, replayed on a
