@@ -823,6 +823,7 @@ int32_t block_take(int device, uint64_t bytes, DeviceBlock* out) {
             }
         }
         for (const DeviceBlock& b : idle) (void)hipFree(b.p);
+        (void)hipGetLastError();
         e = hipMalloc(&p, want);
     }
     if (e != hipSuccess) return fail(SLLM_E_HIP, "hipMalloc(%llu bytes) failed: %s", (unsigned long long)want, hip_message(e));

@@ -127,6 +127,7 @@ void release(sllm_ckpt* h) {
         // a replay may still run: hipFree waits for the device, where the next
         // handle would rewrite a parked block under it
         device_layout_free(&h->layout, /*park=*/!h->captured);
+        (void)hipGetLastError();  // of a call above that was refused
     }
     if (h->keep_table) pool_free_table(h->pool, h->keep_table);
     if (h->pool) {

@@ -143,6 +143,26 @@ def case_open_under_capture():
         assert fake.fake_pending() == 0
 
 
+def case_refused_free():
+    """A close whose hipFree is refused, while another stream captures, leaves no
+    HIP error behind: the next launch of the thread is no failure."""
+    d = convert("c", SIZES)
+    b = Buffers(SIZES, 16, 256)
+    s, other = fake.fake_stream(), fake.fake_stream()
+    ck = binding.Checkpoint(d, dev_alignment=256, ring_slots=1)
+    next_one = binding.Checkpoint(d, dev_alignment=256, ring_slots=1)
+    fake.fake_capture(s, 1)
+    assert b.repack(ck, s) == 0
+    fake.fake_capture(s, 0)
+    fake.fake_capture(other, 1)
+    ck.close()
+    assert b"hipFree" in fake.fake_bad_list()
+    assert fake.fake_pending() == 0
+    assert b.repack(next_one, s) == 0
+    fake.fake_capture(other, 0)
+    next_one.close()
+
+
 def case_failure_under_capture():
     """A repack or load that fails under capture returns its error and makes no
     call that HIP refuses on a capturing stream; eagerly it waits for the stream."""

@@ -147,6 +147,7 @@ hipError_t hipMalloc(void** p, size_t n) {
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+    if (n_capturing && p) return bad("hipFree", hipErrorStreamCaptureUnsupported);
     auto it = device_mem.find((uintptr_t)p);
     if (it == device_mem.end()) return p ? err(hipErrorInvalidValue) : hipSuccess;
     device_used -= it->second;

@@ -35,7 +35,7 @@ def run(fake, tmp_path, case):
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("case", ["events_under_capture", "close_after_capture", "open_under_capture", "failure_under_capture",
+@pytest.mark.parametrize("case", ["events_under_capture", "close_after_capture", "open_under_capture", "refused_free", "failure_under_capture",
                                   "error_not_left_pending", "idle_blocks", "tables_are_checked",
                                   "staging_sizes", "scatter_unroll", "pack_sizes", "plan_writers"])
 def test_host_code(fake, tmp_path, case):
