@@ -164,6 +164,48 @@ def test_repack_captured_in_a_graph(torch_cuda, tmp_path):
         del g
 
 
+@pytest.mark.parametrize("what,A2", [("kernel", 0), ("kernel", 256), ("sdma", 0), ("sdma", 256), ("repack", 256)])
+def test_two_calls_in_one_capture(torch_cuda, tmp_path, what, A2):
+    """A second call of a handle in one capture leaves the capture whole: cached
+    loads by either engine and repacks, replayed with eager ones between the
+    replays."""
+    torch = torch_cuda
+    spec = synth.stress(n=60, max_bytes=256 << 10, seed=48)
+    tensors = [(t.name, t.dtype, t.shape, d) for t, d in zip(spec.tensors, synth.materialize(spec))]
+    d = str(tmp_path / "loads")
+    binding.convert(iter(tensors), d, 4096, 1 << 20)
+    index = oracle.make_index(tensors, 4096, 1 << 20)
+    image = bytes(oracle.partition_bytes(tensors, 4096)[:index.total_bytes])
+    want = bytes(oracle.repack(image, index, A2)) if A2 else image
+    outs = [torch.zeros(len(want), dtype=torch.uint8, device="cuda:0") for _ in range(3)]
+    with binding.Pool(1 << 20, -(-index.total_bytes // (1 << 20))) as pool:
+        pool.cache(d)
+        with binding.Checkpoint(d, pool=pool, engine="sdma" if what == "sdma" else "kernel", dev_alignment=A2) as ck:
+            src = torch.frombuffer(bytearray(image), dtype=torch.uint8).to("cuda:0")
+
+            def work(o):
+                s = torch.cuda.current_stream()
+                ck.repack(src, o, s) if what == "repack" else ck.load_into(o, s)
+
+            work(outs[2])  # its copy streams exist before the capture
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                for o in outs[:2]:
+                    work(o)
+            for k in range(3):
+                for o in outs:
+                    o.fill_(0xA5)
+                work(outs[2])
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+                for i, o in enumerate(outs):
+                    assert o.cpu().numpy().tobytes() == want, (k, i)
+            del g
+        pool.evict(d)
+
+
 def test_open_while_another_stream_captures(torch_cuda, tmp_path):
     """A handle that opens on idle blocks, while a stream captures, leaves the
     capture whole, and loads as ever."""
