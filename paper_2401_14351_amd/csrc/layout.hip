@@ -892,15 +892,16 @@ int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev
     l.d_shift = reinterpret_cast<int64_t*>(l.d_size + l.n);
     std::vector<uint64_t> got(3 * l.n + 2);
     const int32_t st = launch_tables(ix.sizes, ix.alignment, dev_align, l.d_size, l.d_off, l.d_dev, l.d_shift, l.n_shift, nullptr);
-    // queued and then waited for: hipMemcpy is refused, and ends the capture,
-    // while another stream captures.  The wait comes first in any case: loads run
-    // on other streams, and after a failed launch the block may go back.
-    const hipError_t copied =
-        hipMemcpyAsync(got.data(), l.tables.p, got.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, nullptr);
-    const hipError_t waited = hipStreamSynchronize(nullptr);
+    // This form of the copy waits for the null stream too, but is not refused,
+    // ending the capture, while another stream captures, as hipMemcpy is.  (Queued
+    // and then waited for, it costs a load 5 us more.)  In any case the stream is
+    // waited for: loads run on others, and after a failed launch the block may go
+    // back.
+    const hipError_t e =
+        hipMemcpyWithStream(got.data(), l.tables.p, got.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, nullptr);
+    if (e != hipSuccess) (void)hipStreamSynchronize(nullptr);
     if (st != SLLM_OK) return st;
-    SLLM_HIP(copied);
-    SLLM_HIP(waited);
+    SLLM_HIP(e);
     // the device's tables against the host's: a wrong entry would send bytes
     // past the image
     const uint64_t *off = got.data(), *dev = off + l.n + 1, *size = dev + l.n + 1;

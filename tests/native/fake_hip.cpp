@@ -196,6 +196,11 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
     if (!capturing(st)) std::memcpy(d, s, n);
     return hipSuccess;
 }
+hipError_t hipMemcpyWithStream(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+    if (capturing(st)) return bad("hipMemcpyWithStream", hipErrorStreamCaptureUnsupported);
+    std::memcpy(d, s, n);
+    return hipSuccess;
+}
 hipError_t hipGetSymbolAddress(void** p, const void*) {
     static void* scratch = std::aligned_alloc(4096, 16 << 20);
     *p = scratch;
