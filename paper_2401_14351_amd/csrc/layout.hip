@@ -905,11 +905,14 @@ int32_t device_layout_build(const IndexData& ix, int device, const uint64_t* dev
     // the device's tables against the host's: a wrong entry would send bytes
     // past the image
     const uint64_t *off = got.data(), *dev = off + l.n + 1, *size = dev + l.n + 1;
-    for (uint64_t i = 0; i < l.n; ++i)
-        if (off[i] != ix.tensors[i].offset || dev[i] != dev_off[i] || size[i] != ix.sizes[i])
+    uint64_t o = 0;  // o_i, as the index was checked to hold them; its records lie further apart than the sizes
+    for (uint64_t i = 0; i < l.n; ++i) {
+        if (off[i] != o || dev[i] != dev_off[i] || size[i] != ix.sizes[i])
             return fail(SLLM_E_HIP, "device tables disagree at tensor %llu: offset %llu, device offset %llu, size %llu",
                         (unsigned long long)i, (unsigned long long)off[i], (unsigned long long)dev[i],
                         (unsigned long long)size[i]);
+        o += (ix.sizes[i] + ix.alignment - 1) & ~(ix.alignment - 1);
+    }
     if (off[l.n] != ix.total || dev[l.n] != dev_total) return fail(SLLM_E_HIP, "device tables disagree on the totals");
     return SLLM_OK;
 }
