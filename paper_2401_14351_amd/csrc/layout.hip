@@ -77,9 +77,10 @@ __device__ __forceinline__ int64_t plan_entry(uint64_t y, uint64_t dm, uint64_t 
     return y + kPlanBytes <= dm + sm ? (int64_t)(om - dm) : kMixedTile + (int64_t)m;
 }
 
-// Whether a batch of m tensors and `blocks` plan blocks has its plan spread over
-// a grid (k3_tables): beyond four blocks a tensor, and from one on where more
-// than 4 % of the tensors, `runs`, hold more than kTableRun blocks.  Tensor by
+// Whether a batch of m tensors of sizes s and `blocks` plan blocks has its plan
+// spread over a grid (k3_tables): beyond four blocks a tensor, and from one on
+// where more than 4 % of the tensors hold more than kTableRun blocks ("runs",
+// counted only there: a small batch's call is bound by the host).  Tensor by
 // tensor such a run goes round its wave of 128 tensors alone, and the longest of
 // the others holds up the lanes beside it; where all are short, or few are long,
 // it saves the grid's bisection.  Allocation-free repacks, spread / tensor by
@@ -91,8 +92,11 @@ __device__ __forceinline__ int64_t plan_entry(uint64_t y, uint64_t dm, uint64_t 
 // tensors: 1.0 blocks 156.3 / 148.8, 3.0 374.5 / 379.5 and 9.5 / 8.7, 4.0 470.4 /
 // 485.9 and 10.2 / 9.4.  2 % of 1 MiB among small ones, mean 1.4: 232.7 / 226.2.
 constexpr uint64_t kTableRun = 8;
-bool spread_plan(uint64_t blocks, uint64_t m, uint64_t runs) {
-    return blocks > 4 * m || (blocks > m && 25 * runs > m);
+bool spread_plan(uint64_t blocks, const uint64_t* s, uint64_t m) {
+    if (blocks <= m || blocks > 4 * m) return blocks > m;
+    uint64_t runs = 0;
+    for (uint64_t j = 0; j < m; ++j) runs += s[j] > kTableRun * kPlanBytes;
+    return 25 * runs > m;
 }
 
 // One workgroup decodes the sizes, scans both layouts' padded sizes (two
@@ -758,14 +762,13 @@ int32_t launch_tables(const std::vector<uint64_t>& s, uint64_t align, uint64_t d
     for (a.i0 = 0; a.i0 < s.size(); a.i0 += a.m) {
         a.m = pack_sizes(s.data() + a.i0, s.size() - a.i0, &a);
         a.last = a.i0 + a.m == s.size();
-        uint64_t o = a.o0, d = a.d0, runs = 0;
+        uint64_t o = a.o0, d = a.d0;
         for (uint32_t j = 0; j < a.m; ++j) {  // both totals were checked against 64 bits before
-            runs += s[a.i0 + j] > kTableRun * kPlanBytes;
             o += (s[a.i0 + j] + align - 1) & ~(align - 1);
             d += (s[a.i0 + j] + dev_align - 1) & ~(dev_align - 1);
         }
         const uint64_t blocks = std::min(ceil_div(d, kPlanBytes), n_plan) - std::min(a.d0 / kPlanBytes, n_plan);
-        a.spread = spread_plan(blocks, a.m, runs);
+        a.spread = spread_plan(blocks, s.data() + a.i0, a.m);
         // spread: a workgroup for each 1024 blocks of the plan
         const uint32_t grid = a.spread ? (uint32_t)std::min<uint64_t>(512, ceil_div(blocks, 1024)) : 1;
         k3_tables<<<dim3(grid), dim3(1024), 0, stream>>>(a);
